@@ -20,6 +20,10 @@
 #include <vector>
 
 #include "../../include/unet.h"
+#include "unet_conv.h"
+#include "unet_device.h"
+
+using namespace unet;
 
 namespace {
 
@@ -37,29 +41,6 @@ unet_status ufail(unet_status s, const std::string& m) {
       return ufail(e_ == hipErrorOutOfMemory ? UNET_ENOMEM : UNET_EHIP,                  \
                    std::string(#expr) + ": " + hipGetErrorString(e_));                   \
   } while (0)
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-__device__ __forceinline__ float bf2f(uint16_t b) { return __uint_as_float(((uint32_t)b) << 16); }
-__device__ __forceinline__ uint16_t f2bf(float f) {
-  uint32_t u = __float_as_uint(f);
-  u += 0x7FFFu + ((u >> 16) & 1u);
-  return (uint16_t)(u >> 16);
-}
-
-__device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {
-  const uint4 v = *reinterpret_cast<const uint4*>(p);
-  bf16x8 r;
-  __builtin_memcpy(&r, &v, 16);
-  return r;
-}
-__device__ __forceinline__ bf16x8 zero8() {
-  uint4 v = make_uint4(0, 0, 0, 0);
-  bf16x8 r;
-  __builtin_memcpy(&r, &v, 16);
-  return r;
-}
 
 struct Vox {
   int n, d, h, w;
@@ -214,140 +195,6 @@ __global__ __launch_bounds__(256) void k_conv_fwd(unet_shape s, const uint16_t* 
         const long long v = vbase + mb * 16 + 4 * (lane >> 4) + r;
         if (v >= nvox) continue;
         float val = acc[mb][nb][r] + bb;
-        if (relu) val = fmaxf(val, 0.f);
-        if (yf)
-          yf[v * yld + yoff + co] = val;
-        else
-          y[v * yld + yoff + co] = f2bf(val);
-      }
-    }
-}
-
-// The 3x3x3 convolution of CIN (8 to 64) input channels on grids with w a
-// multiple of 64 and h of 4 (TW = 64: output tiles of 64 (w) x 4 (h) voxels
-// of one plane, one row per wave), or w = 32 and h a multiple of 8 (TW = 32:
-// 32 x 8 tiles, two rows per wave, contiguous as the rows are the whole grid
-// width).  The tile's input neighbourhood ((TW + 2) x (TH + 2) x 3 voxels,
-// zeros outside the grid) is staged in LDS once, and every tap's A operand is
-// then read from LDS instead of being gathered from global memory 27 times.
-// The K steps, the operands and the MFMA order are those of k_conv_fwd, so
-// the output is bitwise the same.
-template <int CIN, int NB, int TW = 64>
-__global__ __launch_bounds__(256) void k_conv_fwd_tile(unet_shape s,
-                                                       const uint16_t* __restrict__ x, int xld,
-                                                       int xoff, const uint16_t* __restrict__ w,
-                                                       const float* __restrict__ bias,
-                                                       uint16_t* __restrict__ y, int yld,
-                                                       int yoff, float* __restrict__ yf,
-                                                       int relu) {
-  static_assert(CIN == 8 || CIN == 16 || CIN == 32 || CIN == 64,
-                "tiled conv: 8, 16, 32 or 64 input channels (64: 152 KB of LDS)");
-  static_assert(TW == 64 || TW == 32, "tiled conv: tiles 64 or 32 wide");
-  constexpr int kTW = TW, kTH = 256 / TW, kRW = 64 / TW;  // kRW: rows per wave
-  constexpr int kSW = kTW + 2, kSH = kTH + 2, kSlots = 3 * kSH * kSW;
-  __shared__ __align__(16) uint16_t tile[kSlots * CIN];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int co0 = blockIdx.y * (16 * NB);  // this workgroup's output channels
-  const int tw = s.w / kTW, th = s.h / kTH;
-  int b = blockIdx.x;
-  const int w0 = (b % tw) * kTW;
-  b /= tw;
-  const int h0 = (b % th) * kTH;
-  b /= th;
-  const int d0 = b % s.d, n0 = b / s.d;
-  // stage the neighbourhood: 16-byte pieces of 8 channels, four loads in
-  // flight per thread before their stores
-  constexpr int P8 = CIN / 8, NP = kSlots * P8;
-  for (int p0 = threadIdx.x; p0 < NP; p0 += 4 * 256) {
-    uint4 v[4];
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int p = min(p0 + u * 256, NP - 1);
-      const int slot = p / P8, c8 = p - slot * P8;
-      const int sw = slot % kSW, sh = (slot / kSW) % kSH, sd = slot / (kSW * kSH);
-      const int dd = d0 - 1 + sd, hh = h0 - 1 + sh, ww = w0 - 1 + sw;
-      const bool in = dd >= 0 && dd < s.d && hh >= 0 && hh < s.h && ww >= 0 && ww < s.w;
-      const long long vox = in ? (((long long)n0 * s.d + dd) * s.h + hh) * s.w + ww : 0;
-      const uint4 g = *reinterpret_cast<const uint4*>(x + vox * xld + xoff + c8 * 8);
-      v[u] = in ? g : make_uint4(0, 0, 0, 0);
-    }
-#pragma unroll
-    for (int u = 0; u < 4; ++u) {
-      const int p = p0 + u * 256;
-      if (p < NP) *reinterpret_cast<uint4*>(tile + p * 8) = v[u];
-    }
-  }
-  __syncthreads();
-  constexpr int K = 27 * CIN;
-  constexpr int ksteps = (K + 31) / 32;
-  const int kl = 8 * (lane >> 4);
-  // Operands of K step ks: A (4 voxel blocks) from the LDS tile, B (NB
-  // output blocks) from the weights.  Steps past the end read step ksteps - 1
-  // (never used).
-  auto load_a = [&](int ks, bf16x8 (&a)[4]) {
-    const int k = min(ks, ksteps - 1) * 32 + kl;
-    const bool kin = k < K;
-    const int kk = kin ? k : K - 8;
-    const int t = kk / CIN, ci = kk % CIN;
-    const int dd = t / 9, dh = (t / 3) % 3, dw = t % 3;
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      // the wave's voxel mb * 16 + (lane & 15): row l / TW of its rows
-      const int l = mb * 16 + (lane & 15), row = l / kTW, wl = l % kTW;
-      const int slot = (dd * kSH + kRW * wave + row + dh) * kSW + wl + dw;
-      const bf16x8 v = *reinterpret_cast<const bf16x8*>(tile + slot * CIN + ci);
-      a[mb] = kin ? v : zero8();
-    }
-  };
-  auto load_b = [&](int ks, bf16x8 (&b)[NB]) {
-    const int k = min(ks, ksteps - 1) * 32 + kl;
-    const bool kin = k < K;
-    const int kk = kin ? k : K - 8;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const bf16x8 v = ld8(w + (long long)(co0 + nb * 16 + (lane & 15)) * K + kk);
-      b[nb] = kin ? v : zero8();
-    }
-  };
-  f32x4 acc[4][NB];
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) acc[mb][nb] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // weights PF steps ahead, activations one step ahead; MFMA order as in
-  // k_conv_fwd (K steps in order)
-  constexpr int PF = 4;
-  bf16x8 bq[PF][NB], aq[2][4];
-#pragma unroll
-  for (int u = 0; u < PF; ++u) load_b(u, bq[u]);
-  load_a(0, aq[0]);
-  for (int ks = 0; ks < ksteps; ks += PF) {
-#pragma unroll
-    for (int u = 0; u < PF; ++u) {
-      const int k = ks + u;
-      if (k < ksteps) {
-        load_a(k + 1, aq[(u + 1) & 1]);
-#pragma unroll
-        for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-          for (int nb = 0; nb < NB; ++nb)
-            acc[mb][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aq[u & 1][mb], bq[u][nb],
-                                                                  acc[mb][nb], 0, 0, 0);
-        load_b(k + PF, bq[u]);
-      }
-    }
-  }
-  const long long vbase = (((long long)n0 * s.d + d0) * s.h + h0 + kRW * wave) * s.w + w0;
-#pragma unroll
-  for (int mb = 0; mb < 4; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-      const int co = co0 + nb * 16 + (lane & 15);
-      const float bv = bias ? bias[co] : 0.f;
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const long long v = vbase + mb * 16 + 4 * (lane >> 4) + r;
-        float val = acc[mb][nb][r] + bv;
         if (relu) val = fmaxf(val, 0.f);
         if (yf)
           yf[v * yld + yoff + co] = val;
@@ -1189,18 +1036,16 @@ long long wgrad_chunk(long long nvox) {
 }
 
 
-// Launch plan of the forward convolution (and of the data gradient, which is
-// a forward convolution).
+// Size classes of a forward convolution (and of the data gradient, which is
+// a forward convolution), as unet_conv_kernel reports them:
 //   CONV_TILE:   3x3x3 taps, 8, 16, 32 or 64 input channels, 16-64 output
-//                channels, w a multiple of 64 and h of 4 (64 x 4 tiles) or
-//                w = 32 and h a multiple of 8 (32 x 8 tiles): LDS tiles.
-//   CONV_GATHER: everything else: 64 (or 16) voxels per wave, operands
-//                gathered from global memory.
-// Both split the output channels over workgroups while the grid would leave
-// CUs without work (tiles: until every CU has as many workgroups as its LDS
-// holds).  Measured on 32^3 grids: tiles with 32 -> 64 channels 188 -> 302
-// TFLOP/s, 64 -> 64 220 -> 308; gathered 16^3 grids 18-21 -> 54-88, 32^3
-// with 128 channels 105-126 -> 170-180.
+//                channels, w a multiple of 64 and h of 4, or w = 32 and h a
+//                multiple of 8.
+//   CONV_GATHER: everything else.
+// Both with a blocking that splits the output channels while the grid would
+// leave CUs without work.  The gathered kernel (1x1x1 taps; planes too large
+// for the brick kernel's 32-bit offsets) runs that blocking, in class
+// CONV_TILE with 64 voxels per wave.
 enum { CONV_GATHER = 0, CONV_TILE = 1 };
 struct ConvPlan {
   int kind, mb, nb, tw;
@@ -1216,6 +1061,7 @@ ConvPlan conv_plan(unet_shape s, int cin, int cout, int taps) {
       (cin == 8 || cin == 16 || cin == 32 || cin == 64)) {
     p.kind = CONV_TILE;
     p.tw = t64 ? 64 : 32;
+    p.mb = 4;  // of the gathered kernel
     const int th = 256 / p.tw;
     const long long tiles = nv / 256;
     const long long lds = 3LL * (th + 2) * (p.tw + 2) * cin * 2;
@@ -1239,6 +1085,126 @@ ConvPlan conv_plan(unet_shape s, int cin, int cout, int taps) {
     p.grid = (nv + 64 * p.mb - 1) / (64 * p.mb);
   }
   return p;
+}
+
+// Launch plan of the brick kernel (3x3x3 taps): rows per wave, waves along d
+// and along the output channels.
+struct BrickShape {
+  int mb, wd, wc;
+};
+constexpr BrickShape kBricks[] = {{8, 4, 1}, {8, 2, 2}, {8, 1, 4}, {4, 1, 2}, {4, 2, 1}};
+constexpr int kNBricks = 5;
+
+// Chunk size and chunks per pass: all channels at once for 64 and 128.
+void brick_chunks(int cin, int* ck, int* nc) {
+  *ck = cin % 32 == 0 ? 32 : (cin % 16 == 0 ? 16 : 8);
+  *nc = cin == 128 ? 4 : (cin == 64 ? 2 : 1);
+}
+
+// Microseconds a CU spends on one work item (with one chunk per pass: on one
+// pass), by shape and 8, 16, 32, 64 or 128 channels, with one output block per
+// wave and with two; 0: no such instance.  Measured on the U-Net's layers of
+// 128^3 and 48 x 56 x 104 inputs with every instance (also 4 x 4 waves along d,
+// 4 rows x 4 waves along the channels, and two output blocks with 32 channels
+// and more, none of which was the fastest anywhere by more than 4 %).
+constexpr double kBrickUs[2][kNBricks][5] = {{{2.1, 2.8, 4.7, 0, 0},
+                                              {0, 0, 4.4, 9.0, 20.0},
+                                              {0, 0, 4.3, 8.3, 15.5},
+                                              {0, 0, 2.2, 4.1, 7.8},
+                                              {0.55, 0.93, 1.8, 4.7, 9.0}},
+                                             {{3.3, 4.8, 0, 0, 0},
+                                              {0, 0, 0, 0, 0},
+                                              {0, 0, 0, 0, 0},
+                                              {0, 0, 0, 0, 0},
+                                              {0.9, 1.6, 0, 0, 0}}};
+constexpr int brick_class(int ck, int nc) {
+  return ck == 8 ? 0 : (ck == 16 ? 1 : (nc == 1 ? 2 : (nc == 2 ? 3 : 4)));
+}
+constexpr bool brick_exists(int shape, int ck, int nc, int nb) {
+  return kBrickUs[nb - 1][shape][brick_class(ck, nc)] > 0;
+}
+
+struct BrickPlan {
+  int ck, nc, shape, nb;  // shape < 0: no brick kernel for these sizes
+  int nbw, nbh, nbd;
+};
+
+// The instance with the least estimated time (work items in rounds of 256 CUs,
+// times kBrickUs): the fastest one on the grids measured, or within 8 % of it.
+// Every instance gives bitwise the same result (8 to 128 channels in powers of
+// two: all products in (tap, channel) order).
+BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
+  BrickPlan best{};
+  best.shape = -1;
+  // staging offsets and work items are 32-bit
+  if ((long long)8 * s.h * s.w * xld * 2 >= (1LL << 31) - 16) return best;
+  int ck, nc;
+  brick_chunks(cin, &ck, &nc);
+  double tbest = 0.0;
+  for (int sh = 0; sh < kNBricks; ++sh) {
+    const BrickShape& b = kBricks[sh];
+    for (int nb = 1; nb <= 2; ++nb) {
+      if (!brick_exists(sh, ck, nc, nb) || (cout / 16) % (nb * b.wc)) continue;
+      const int nbw = (s.w + 15) / 16, nbh = (s.h + b.mb - 1) / b.mb, nbd = (s.d + b.wd - 1) / b.wd;
+      const double items = (double)s.n * nbw * nbh * nbd * (cout / 16 / nb / b.wc);
+      const double t = std::ceil(items / 256.0) * kBrickUs[nb - 1][sh][brick_class(ck, nc)];
+      if (items < 2e9 && (best.shape < 0 || t < tbest)) {
+        tbest = t;
+        best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd};
+      }
+    }
+  }
+  //FORCE
+  return best;
+}
+
+template <int CK, int NC, int NB, int SHAPE>
+void launch_brick(const ConvArgs& a, hipStream_t st) {
+  if constexpr (brick_exists(SHAPE, CK, NC, NB)) {
+    constexpr BrickShape b = kBricks[SHAPE];
+    using B = Brick<CK, NC, b.mb, NB, b.wd, b.wc>;
+    // as many workgroups as run at once
+    hipLaunchKernelGGL((k_conv_brick<CK, NC, b.mb, NB, b.wd, b.wc>),
+                       dim3((unsigned)std::min(a.total, 256 * std::max(1, B::PER_CU))), dim3(B::NT),
+                       0, st, a);
+  }
+}
+
+template <int CK, int NC, int NB>
+void launch_bricks(int shape, const ConvArgs& a, hipStream_t st) {
+  switch (shape) {
+    case 0: launch_brick<CK, NC, NB, 0>(a, st); break;
+    case 1: launch_brick<CK, NC, NB, 1>(a, st); break;
+    case 2: launch_brick<CK, NC, NB, 2>(a, st); break;
+    case 3: launch_brick<CK, NC, NB, 3>(a, st); break;
+    default: launch_brick<CK, NC, NB, 4>(a, st); break;
+  }
+}
+
+void enq_brick(const BrickPlan& p, ConvArgs a, int cout, hipStream_t st) {
+  a.nbw = p.nbw;
+  a.nbh = p.nbh;
+  a.nbd = p.nbd;
+  a.groups = cout / 16 / p.nb / kBricks[p.shape].wc;
+  a.total = (int)((long long)a.s.n * p.nbw * p.nbh * p.nbd * a.groups);
+  if (p.ck == 32) {
+    if (p.nc == 4)
+      launch_bricks<32, 4, 1>(p.shape, a, st);
+    else if (p.nc == 2)
+      launch_bricks<32, 2, 1>(p.shape, a, st);
+    else
+      launch_bricks<32, 1, 1>(p.shape, a, st);
+  } else if (p.ck == 16) {
+    if (p.nb == 2)
+      launch_bricks<16, 1, 2>(p.shape, a, st);
+    else
+      launch_bricks<16, 1, 1>(p.shape, a, st);
+  } else {
+    if (p.nb == 2)
+      launch_bricks<8, 1, 2>(p.shape, a, st);
+    else
+      launch_bricks<8, 1, 1>(p.shape, a, st);
+  }
 }
 
 // Groups of 64 chunk rows summed first when there are more than 64 rows.
@@ -1351,8 +1317,30 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
   const int ob = y.c / 16;
   if (ob != 1 && ob != 2 && ob != 4 && ob != 8)
     return ufail(UNET_EINVAL, "output channels must be 16, 32, 64 or 128");
-  const ConvPlan p = conv_plan(s, x.c, y.c, taps);
   hipStream_t st = (hipStream_t)stream;
+  if (taps == 27) {
+    const BrickPlan bp = brick_plan(s, x.c, x.ld, y.c);
+    if (bp.shape >= 0) {
+      ConvArgs a{};
+      a.s = s;
+      a.x = (const uint16_t*)x.p;
+      a.xld = x.ld;
+      a.xoff = x.off;
+      a.cin = x.c;
+      a.w = (const uint16_t*)w;
+      a.bias = bias;
+      a.y = (uint16_t*)y.p;
+      a.yld = y.ld;
+      a.yoff = y.off;
+      a.yf = out_f32;
+      a.relu = relu;
+      a.wide = (uintptr_t)(out_f32 ? (void*)out_f32 : y.p) % 16 == 0;
+      enq_brick(bp, a, y.c, st);
+      UHIP(hipGetLastError());
+      return UNET_OK;
+    }
+  }
+  const ConvPlan p = conv_plan(s, x.c, y.c, taps);
   const uint16_t* xp = (const uint16_t*)x.p;
   const uint16_t* wp = (const uint16_t*)w;
   uint16_t* yp = (uint16_t*)y.p;
@@ -1365,40 +1353,15 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
       default: fn(std::integral_constant<int, 8>{}); break;
     }
   };
-  if (p.kind == CONV_TILE) {
-    auto go = [&](auto cinc) {
-      constexpr int CIN = decltype(cinc)::value;
-      nbs([&](auto nbc) {
-        constexpr int NB = decltype(nbc)::value;
-        if constexpr (NB <= 4) {
-          if (p.tw == 64)
-            hipLaunchKernelGGL((k_conv_fwd_tile<CIN, NB, 64>), grid, dim3(256), 0, st, s, xp,
-                               x.ld, x.off, wp, bias, yp, y.ld, y.off, out_f32, relu);
-          else
-            hipLaunchKernelGGL((k_conv_fwd_tile<CIN, NB, 32>), grid, dim3(256), 0, st, s, xp,
-                               x.ld, x.off, wp, bias, yp, y.ld, y.off, out_f32, relu);
-        }
-      });
-    };
-    if (x.c == 8)
-      go(std::integral_constant<int, 8>{});
-    else if (x.c == 16)
-      go(std::integral_constant<int, 16>{});
-    else if (x.c == 32)
-      go(std::integral_constant<int, 32>{});
-    else
-      go(std::integral_constant<int, 64>{});
-  } else {
-    nbs([&](auto nbc) {
-      constexpr int NB = decltype(nbc)::value;
-      if (p.mb == 4)
-        hipLaunchKernelGGL((k_conv_fwd<4, NB>), grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c,
-                           wp, bias, taps, yp, y.ld, y.off, out_f32, relu);
-      else if constexpr (NB <= 2)
-        hipLaunchKernelGGL((k_conv_fwd<1, NB>), grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c,
-                           wp, bias, taps, yp, y.ld, y.off, out_f32, relu);
-    });
-  }
+  nbs([&](auto nbc) {
+    constexpr int NB = decltype(nbc)::value;
+    if (p.mb == 4)
+      hipLaunchKernelGGL((k_conv_fwd<4, NB>), grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, wp,
+                         bias, taps, yp, y.ld, y.off, out_f32, relu);
+    else if constexpr (NB <= 2)
+      hipLaunchKernelGGL((k_conv_fwd<1, NB>), grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, wp,
+                         bias, taps, yp, y.ld, y.off, out_f32, relu);
+  });
   UHIP(hipGetLastError());
   return UNET_OK;
 }
