@@ -116,13 +116,15 @@ typedef struct gmg_params {
                             consecutive red-black sweeps of one smoothing step
                             run as one two-sweep pass (temporal blocking: the
                             faces and sigma are read once for both sweeps),
-                            bitwise the same result.  On at level 0 by
-                            default; gmg_autotune and gmg_set_pair_sweeps
-                            choose per level.  Needs FP32 cycles, the
+                            bitwise the same result.  Small levels (up to
+                            2^18 to 2^19 cells, also in FP64 and with an odd
+                            nx) run them on cubes held in LDS, the others as
+                            marching passes, which need FP32 cycles, the
                             red-black smoother, an even nx and at most 2^28
-                            cells on the level (32-bit buffer offsets); the
-                            deferred norm's sweeps stay single.  0: separate
-                            sweeps.                                           */
+                            cells on the level (32-bit buffer offsets);
+                            gmg_autotune and gmg_set_pair_sweeps choose per
+                            level.  The deferred norm's first sweeps stay
+                            passes or single.  0: separate sweeps.            */
   double omega0;         /* relaxation factor at the start of a solve (1.0)   */
   double omega_min;      /* lower bound (0.1)                                 */
   double omega_max;      /* upper bound (1.0)                                 */
@@ -455,7 +457,8 @@ typedef struct gmg_tune_report {
  * {8, 4} and kchunk in {2, 4, ..., 64} up to nz, FP64 cycles: ty 4; and the
  * split half-sweeps, ty 1), and where pair_sweeps allows, `reps` two-sweep
  * passes with ty in {16, 8} and kchunk in {default, 4, 8, ..., 256} (a pass
- * is kept if it beats two of the chosen sweeps), with
+ * is kept if it beats two of the chosen sweeps and, on small levels, two
+ * sweeps on cubes, which stay otherwise: pair_kchunk 0), with
  * HIP events on the handle's stream, and keep the fastest per level.  x and
  * sigma are level-0 device arrays (dtype == cycle_dtype) used as the sweep's
  * input (x is overwritten with smoothed values; coarse levels use internal
@@ -472,7 +475,8 @@ gmg_status gmg_set_tiles(gmg_handle* h, int32_t level, int32_t ty, int32_t kchun
 
 /* Run the smoothing steps of one level with two-sweep passes on tiles of
  * 64 x ty cells (ty 8 or 16) with kchunk z-planes per workgroup (kchunk = 0:
- * separate sweeps, ty ignored).  GMG_EINVAL if the handle's parameters do not
+ * separate sweeps, or two at a time on cubes where pair_sweeps = 1 and the
+ * level is small enough for them; ty ignored).  GMG_EINVAL if the handle's parameters do not
  * allow passes (pair_sweeps 0, FP64 cycles, the PCG smoother, an odd nx or
  * more than 2^28 cells on the level),
  * ty is not 8 or 16, or kchunk is outside [0, nz].  Results do not depend on

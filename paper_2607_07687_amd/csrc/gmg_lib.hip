@@ -24,6 +24,7 @@
 #include <vector>
 
 #include "gmg_kernels.h"
+#include "gmg_cube.h"
 #include "gmg_sweep.h"
 #include "gmg_sweep2.h"
 #include "gmg_tail.h"
@@ -818,6 +819,7 @@ struct Level {
   int pair_kc;     // > 0: two consecutive sweeps run as one two-sweep pass
                    // with this z-chunk; 0: separate sweeps
   int pair_ty;     // tile rows of the two-sweep pass (8 or 16)
+  int cube;        // 1: two consecutive sweeps run on LDS cubes (gmg_cube.h)
   UBrick* ub;      // uniform-brick map (NULL: off); ubx x uby x ubz bricks
   int ubx, uby, ubz;
   S2TileMode* tm;  // face modes of the two-sweep pass's tiles (NULL: none)
@@ -862,6 +864,23 @@ bool pair_capable(const gmg_params& p, const Geom& g) {
   return p.pair_sweeps && p.cycle_dtype == GMG_F32 && p.smoother == GMG_SMOOTH_RBGS &&
          g.nx % 2 == 0 && g.n <= S2_MAX_CELLS &&
          (p.nu_pre >= 2 || p.nu_post >= 2 || p.nu_coarse >= 2);
+}
+
+// Whether a level's consecutive sweeps run on LDS cubes (gmg_cube.h) by
+// default: small levels, where a launch's latency counts and not the halo each
+// cube recomputes.  Two sweeps from Python, us, cubes against the two-sweep
+// pass (FP32) or two fused sweeps (FP64, odd nx):
+//   32^3      FP32 10.2 / 16.1   FP64 11.2 / 23.7
+//   64^3           14.5 / 17.4        21.3 / 26.4
+//   96x64x64       20.2 / 18.0        29.3 / 34.1
+//   104x72x56      22.1 / 17.9        38.4 / 34.9
+//   33x47x51       12.7 / 24.5        14.3 / 31.6
+//   75x81x101      41.6 / 40.7        58.9 / 68.3
+constexpr long long kCubeCellsPair = 5LL << 16, kCubeCells = 6LL << 16, kCubeCellsOdd = 1LL << 19;
+bool cube_level(const gmg_params& p, const Geom& g) {
+  const long long most = g.nx % 2 ? kCubeCellsOdd
+                                  : (pair_capable(p, g) ? kCubeCellsPair : kCubeCells);
+  return p.pair_sweeps && p.smoother == GMG_SMOOTH_RBGS && g.n <= most;
 }
 
 // z-chunk of the two-sweep pass: one workgroup per CU (its register
@@ -1137,8 +1156,36 @@ static void enq_sweep(gmg_handle* h, int l, const Roles<T>& X, int rs, int rd, c
     launch_sweep<T, TL, 8>(h, l, X, rs, rd, sigma, xc, done, lv.kchunk, o);
 }
 
+// Two consecutive sweeps of level l on LDS cubes: X[rd] =
+// sweep(sweep(X[rs] (+ P x_c))), bitwise the result of two sweeps; rd != rs.
+template <typename T, typename TL>
+static void launch_cube(gmg_handle* h, int l, const Roles<T>& X, int rs, int rd, const T* sigma,
+                        const T* xc, const int* done) {
+  const Level& lv = h->lev[l];
+  const Geom gc = (xc && l + 1 < h->nlev) ? h->lev[l + 1].g : lv.g;
+  const int cx = lv.c[0] ? lv.c[0] : 1, cy = lv.c[1] ? lv.c[1] : 1, cz = lv.c[2] ? lv.c[2] : 1;
+  const dim3 grid(((lv.g.nx + CU_B - 1) / CU_B) * ((lv.g.ny + CU_B - 1) / CU_B) *
+                  ((lv.g.nz + CU_B - 1) / CU_B));
+  auto go = [&](auto vec, auto prol) {
+    hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value>), grid,
+                       dim3(CU_NT), 0, h->s, lv.g, X, rs, rd, sigma, (const TL*)lv.L, xc,
+                       lv.active, gc, cx, cy, cz, &h->st->omega, done);
+  };
+  auto prol = [&](auto vec) {
+    if (xc != nullptr)
+      go(vec, std::true_type{});
+    else
+      go(vec, std::false_type{});
+  };
+  if (lv.g.nx % 2 == 0)
+    prol(std::integral_constant<int, 2>{});
+  else
+    prol(std::integral_constant<int, 1>{});
+}
+
 // nu sweeps of level l from role r (the first with the folded correction
-// x_c), consecutive pairs as two-sweep passes where the level uses them;
+// x_c), consecutive pairs on cubes or as two-sweep passes where the level
+// uses them;
 // each launch writes the other role.  Returns the role of the result.
 template <typename T, typename TL>
 static int enq_sweeps(gmg_handle* h, int l, const Roles<T>& X, int r, const T* sigma, const T* xc,
@@ -1147,7 +1194,10 @@ static int enq_sweeps(gmg_handle* h, int l, const Roles<T>& X, int r, const T* s
   for (int s = 0; s < nu;) {
     const int rd = next_role(l, r);
     const T* c = (s == 0) ? xc : nullptr;
-    if (nu - s >= 2 && lv.pair_kc > 0) {
+    if (nu - s >= 2 && lv.cube) {
+      launch_cube<T, TL>(h, l, X, r, rd, sigma, c, done);
+      s += 2;
+    } else if (nu - s >= 2 && lv.pair_kc > 0) {
       launch_pair<T, TL>(h, l, X, r, rd, sigma, c, done, lv.pair_ty, lv.pair_kc);
       s += 2;
     } else {
@@ -1166,7 +1216,7 @@ static int enq_sweeps(gmg_handle* h, int l, const Roles<T>& X, int r, const T* s
 static int zper_after_passes(const gmg_handle* h, int l, int nu, int planes_per_block, int nzb) {
   const Level& lv = h->lev[l];
   const int kc = lv.pair_kc;
-  if (kc <= 0 || nu < 2 || nu % 2 != 0 || kc % planes_per_block != 0) return 1;
+  if (lv.cube || kc <= 0 || nu < 2 || nu % 2 != 0 || kc % planes_per_block != 0) return 1;
   const int per = kc / planes_per_block;
   return (per > 1 && nzb % per == 0 && (long long)per * planes_per_block * (nzb / per) == lv.g.nz)
              ? per
@@ -1724,13 +1774,16 @@ static gmg_status setup_impl(const gmg_params* p, const void* L, void* stream, g
     }
     lv.ty = p->cycle_dtype == GMG_F64 ? SweepTY<double>::v : SweepTY<float>::v;
     lv.kchunk = sweep_kchunk(lv.g, lv.ty, p->cycle_dtype == GMG_F64 ? 8 : 4);
-    // two-sweep passes: on by default at level 0, where a pass streams the
-    // largest arrays; the autotuner decides for the other levels
+    // two-sweep passes: by default on every level without cubes (128^3: a pass
+    // takes 25-29 us, two fused sweeps 51); the autotuner may choose otherwise
     lv.pair_ty = kPairTYDefault;
+    lv.cube = cube_level(*p, lv.g);
     const bool mapped =
         p->uniform_bricks == 2 || (p->uniform_bricks == 1 && lv.g.n >= kUniformPassCells);
     lv.pair_kc =
-        (l == 0 && pair_capable(*p, lv.g)) ? pair_kchunk(lv.g, lv.pair_ty, mapped ? 2 : 1) : 0;
+        (l == 0 || !lv.cube) && pair_capable(*p, lv.g)
+            ? pair_kchunk(lv.g, lv.pair_ty, mapped ? 2 : 1)
+            : 0;
   }
   maxpart = nblocks(red_grid(h->lev[0].g));
   h->maxpart = maxpart;
@@ -1990,6 +2043,25 @@ static gmg_status autotune_impl(gmg_handle* h, void* x, const void* sigma, int r
       rep->pair_kchunk[l] = lv.pair_kc;
       rep->pair_ty[l] = lv.pair_ty;
       rep->us_pair[l] = 1e3 * pbest;
+    }
+    // small levels keep their cubes unless a pass beats them
+    lv.cube = cube_level(h->p, lv.g);
+    if (lv.cube && lv.pair_kc) {
+      const T* xc = (l + 1 < h->nlev) ? (const T*)h->lev[l + 1].x[0] : nullptr;
+      float cost = 0.f;
+      for (int fold = 0; fold < 2; ++fold) {
+        const T* c = fold ? xc : nullptr;
+        launch_cube<T, TL>(h, l, X, 0, 1, sg, c, nullptr);  // warm-up
+        HIP_TRY(hipEventRecord(e0, h->s));
+        for (int r = 0; r < reps; ++r) launch_cube<T, TL>(h, l, X, 0, 1, sg, c, nullptr);
+        HIP_TRY(hipEventRecord(e1, h->s));
+        HIP_TRY(hipEventSynchronize(e1));
+        float ms = 0.f;
+        HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
+        cost += ms / reps;
+      }
+      lv.cube = 0.5f * cost < 1e-3f * (float)rep->us_pair[l];
+      if (lv.cube) rep->pair_kchunk[l] = 0;
     }
   }
   (void)hipEventDestroy(e0);
@@ -2565,6 +2637,7 @@ gmg_status gmg_set_pair_sweeps(gmg_handle* h, int32_t level, int32_t ty, int32_t
                 "two-sweep passes need pair_sweeps = 1, FP32 cycles, the red-black smoother "
                 "and an even nx");
   if (kchunk < 0 || kchunk > h->lev[level].g.nz) return fail(GMG_EINVAL, "kchunk out of range");
+  h->lev[level].cube = kchunk == 0 && cube_level(h->p, h->lev[level].g);
   h->lev[level].pair_kc = kchunk;
   if (kchunk != 0) h->lev[level].pair_ty = ty;
   refresh_pass_modes(h);

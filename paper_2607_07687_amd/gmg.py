@@ -585,7 +585,8 @@ def gmg_set_tiles(h, level, ty, kchunk):
 
 def gmg_set_pair_sweeps(h, level, kchunk, ty=16):
     """Two-sweep passes on 64 x ty tiles (ty 8 or 16) of kchunk z-planes per
-    workgroup on one level (kchunk 0: separate sweeps)."""
+    workgroup on one level (kchunk 0: separate sweeps, or cubes where the level
+    is small enough)."""
     _check(load().gmg_set_pair_sweeps(h.ptr, int(level), int(ty), int(kchunk)))
 
 
