@@ -377,7 +377,8 @@ struct gmg_batch {
                     // staged in LDS first, then those run in global memory
   int ntail;
   int ntail_lds;    // of which staged in LDS
-  int tail_lds;     // dynamic LDS of k_tail_batch (the largest tail)
+  int tail_lds;     // dynamic LDS of k_tail_batch (the largest tail staged there)
+  int gtail_lds;    // and of the tails run in global memory
   int storage;      // GMG_F32 or GMG_BF16
   gmg_params p0;
   // device descriptor tables
@@ -467,7 +468,8 @@ gmg_status batch_build_tables(gmg_batch* b) {
     if (lt < h->nlev) {
       int bytes = 0;
       (h->tail_global ? gtails : tails).push_back(tail_args<float, TL>(h, lt, &h->st->done, &bytes));
-      tail_lds = std::max(tail_lds, bytes);
+      int& lds = h->tail_global ? b->gtail_lds : tail_lds;
+      lds = std::max(lds, bytes);
     }
     // level-0 residual / update tiles in the same order as the single-problem grid
     const Level& L0 = h->lev[0];
@@ -671,7 +673,7 @@ gmg_status batch_enqueue_solve(gmg_batch* b, hipStream_t s, bool head, double rt
                            (const TailArgs<float, TL>*)b->tails);
       if (b->ntail > b->ntail_lds)
         hipLaunchKernelGGL((k_tail_batch<float, TL, true>), dim3(b->ntail - b->ntail_lds),
-                           dim3(kTailThreads), 0, s,
+                           dim3(kTailThreads), b->gtail_lds, s,
                            (const TailArgs<float, TL>*)b->tails + b->ntail_lds);
       for (int l = b->depth - 1; l >= 0; --l) {  // ascent (coarsest levels finish smoothing)
         int r = role[l];

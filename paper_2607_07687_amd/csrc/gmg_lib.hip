@@ -1340,6 +1340,23 @@ static TailArgs<T, TL> tail_args(gmg_handle* h, int lt, const int* done, int* ld
   a.omega = &h->st->omega;
   a.done = done;
   a.sweeps = &h->st->coarse_sweeps;
+  // register-resident smoothing of the levels whose pairs fit and whose
+  // colour arrays find room in LDS (deepest level first: it has most sweeps)
+  long long total = h->tail_global ? 0 : tail_bytes<T, TL>(h, lt);
+  int xbytes[kTailMax] = {};
+  for (int q = a.nl - 1; q >= 0; --q) {
+    const Geom& g = h->lev[lt + q].g;
+    const long long pairs = (g.nx + 1LL) / 2 * g.ny * g.nz;
+    xbytes[q] = h->tail_global ? 0 : tail_round16(g.n * (long long)sizeof(T));
+    if (pairs > kRegPairs) continue;
+    const int slots = pairs > kTailThreads ? 2 : 1;
+    const int need = std::max(xbytes[q], tail_round16(2LL * (int)sizeof(T) *
+                                                      reg_colour(slots, kTailThreads)));
+    if (total + need - xbytes[q] > kTailLds) continue;
+    total += need - xbytes[q];
+    xbytes[q] = need;
+    a.lv[q].reg = slots;
+  }
   int off = 0;
   for (int q = 0; q < a.nl; ++q) {
     const Level& lv = h->lev[lt + q];
@@ -1352,10 +1369,13 @@ static TailArgs<T, TL> tail_args(gmg_handle* h, int lt, const int* done, int* ld
     t.cx = lv.c[0] ? lv.c[0] : 1;
     t.cy = lv.c[1] ? lv.c[1] : 1;
     t.cz = lv.c[2] ? lv.c[2] : 1;
-    if (h->tail_global) continue;
-    const long long n = lv.g.n;
     t.ox = off;
-    t.os = t.ox + tail_round16(n * (long long)sizeof(T));
+    if (h->tail_global) {
+      off += xbytes[q];
+      continue;
+    }
+    const long long n = lv.g.n;
+    t.os = t.ox + xbytes[q];
     t.oL = t.os + tail_round16(n * (long long)sizeof(T));
     t.oa = t.oL + tail_round16(3 * n * (long long)sizeof(TL));
     off = t.oa + tail_round16(n);
@@ -1369,7 +1389,7 @@ static void enq_tail(gmg_handle* h, int lt, const int* done) {
   int off = 0;
   const TailArgs<T, TL> a = tail_args<T, TL>(h, lt, done, &off);
   if (h->tail_global)
-    hipLaunchKernelGGL((k_tail<T, TL, true>), dim3(1), dim3(kTailThreads), 0, h->s, a);
+    hipLaunchKernelGGL((k_tail<T, TL, true>), dim3(1), dim3(kTailThreads), off, h->s, a);
   else
     hipLaunchKernelGGL((k_tail<T, TL, false>), dim3(1), dim3(kTailThreads), off, h->s, a);
 }

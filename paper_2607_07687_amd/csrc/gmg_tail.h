@@ -47,6 +47,7 @@ struct TailLevel {
   const uint8_t* active;
   int cx, cy, cz;   // factors to the next level
   int ox, os, oL, oa;  // byte offsets of x, sigma, faces, mask in LDS
+  int reg;          // pairs per thread of the register-resident smoothing (0: from LDS)
 };
 
 template <typename T, typename TL>
@@ -210,11 +211,11 @@ __device__ __forceinline__ void tail_prolong(const TailView<T, TL>& f, const Tai
   __syncthreads();
 }
 
-// The coarsest level is smoothed by a group of threads: the workgroup's
-// first wavefront alone when the level has at most kWaveCells cells (its
-// cells do not fill more, and between two half-sweeps a wavefront needs only
-// its own memory operations completed: a fence, no barrier), else the whole
-// workgroup.  The group's stride STRIDE names it.
+// A level is smoothed by a group of threads: the workgroup's first wavefront
+// alone when the coarsest level's cells fill no more (between two half-sweeps
+// a wavefront needs only its own memory operations completed: a fence, no
+// barrier), else the whole workgroup.  The group's stride STRIDE names it; the
+// mean of a level of at most kWaveCells cells is always taken by the wavefront.
 constexpr int kWave = 64;
 constexpr int kWaveCells = 256;
 
@@ -253,44 +254,30 @@ __device__ __forceinline__ double grp_sum(double v, double* red) {
   }
 }
 
-// Half-sweep of colour `colour` by the group, in place: work items are
-// x-pairs of a row, each holding exactly one cell per colour.
-template <typename T, typename TL, int STRIDE>
-__device__ __forceinline__ void grp_half_sweep(const TailView<T, TL>& v, int colour, T omega) {
-  const Geom& g = v.g;
-  const int nx = g.nx, ny = g.ny;
-  const int sy = nx, sz = nx * ny, n = sz * g.nz;
-  const int pr = (nx + 1) >> 1;
-  const int np = pr * ny * g.nz;
-  const float rpr = 1.0f / (float)pr, rny = 1.0f / (float)ny;
-  const TL* Lx = v.L;
-  const TL* Ly = v.L + n;
-  const TL* Lz = v.L + 2 * n;
-  T* x = v.x;
-  for (int p = threadIdx.x; p < np; p += STRIDE) {
-    const int row = tail_div(p, pr, rpr);
-    const int m = p - row * pr;
-    const int k = tail_div(row, ny, rny);
-    const int j = row - k * ny;
-    const int i = 2 * m + ((j + k + colour) & 1);
-    if (i >= nx) continue;
-    const int q = row * nx + i;
-    const bool xe_in = i + 1 < nx || g.px, xw_in = i > 0 || g.px;
-    const bool yn_in = j + 1 < ny || g.py, ys_in = j > 0 || g.py;
-    const bool zt_in = k + 1 < g.nz || g.pz, zb_in = k > 0 || g.pz;
-    const int qe = (i + 1 < nx) ? q + 1 : q - (nx - 1);
-    const int qw = (i > 0) ? q - 1 : q + (nx - 1);
-    const int qn = (j + 1 < ny) ? q + sy : q - (ny - 1) * sy;
-    const int qs = (j > 0) ? q - sy : q + (ny - 1) * sy;
-    const int qt = (k + 1 < g.nz) ? q + sz : q - (g.nz - 1) * sz;
-    const int qb = (k > 0) ? q - sz : q + (g.nz - 1) * sz;
-    x[q] = relax_cell<T>(x[q], xe_in ? x[qe] : T(0), xw_in ? x[qw] : T(0), yn_in ? x[qn] : T(0),
-                         ys_in ? x[qs] : T(0), zt_in ? x[qt] : T(0), zb_in ? x[qb] : T(0),
-                         ldL<T>(Lx, q), xe_in ? ldL<T>(Lx, qe) : T(0), ldL<T>(Ly, q),
-                         yn_in ? ldL<T>(Ly, qn) : T(0), ldL<T>(Lz, q),
-                         zt_in ? ldL<T>(Lz, qt) : T(0), v.s[q], omega);
-  }
-  grp_sync<STRIDE>();
+// Sum over the wavefront in every lane's result: within rows of 16 lanes by
+// DPP moves, then the four rows in order.
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+  const uint32_t l2 = (uint32_t)__builtin_amdgcn_update_dpp(lo, lo, CTRL, 0xf, 0xf, false);
+  const uint32_t h2 = (uint32_t)__builtin_amdgcn_update_dpp(hi, hi, CTRL, 0xf, 0xf, false);
+  return v + __builtin_bit_cast(double, (uint64_t)h2 << 32 | l2);
+}
+__device__ __forceinline__ double wave_sum_rows(double v) {
+  v = dpp_add<0xB1>(v);   // quad: lanes 1 0 3 2
+  v = dpp_add<0x4E>(v);   // quad: lanes 2 3 0 1
+  v = dpp_add<0x141>(v);  // half row mirrored
+  v = dpp_add<0x140>(v);  // row mirrored
+  const uint64_t u = __builtin_bit_cast(uint64_t, v);
+  const int lo = (int)(uint32_t)u, hi = (int)(uint32_t)(u >> 32);
+  double s = 0.0;
+#pragma unroll
+  for (int r = 0; r < kWave; r += 16)
+    s += __builtin_bit_cast(double,
+                            (uint64_t)(uint32_t)__builtin_amdgcn_readlane(hi, r) << 32 |
+                                (uint32_t)__builtin_amdgcn_readlane(lo, r));
+  return s;
 }
 
 // Residual of cell q of a tail level (dtype arithmetic); `act` is D != 0.
@@ -309,19 +296,19 @@ __device__ __forceinline__ T tail_cell_residual(const TailView<T, TL>& v, int q,
 }
 
 // ||sigma - A x||_2 over the active cells: FP64 squares of the dtype
-// residuals summed per thread in cell order, then over the group.
-template <typename T, typename TL, int STRIDE>
-__device__ __forceinline__ double grp_resnorm(const TailView<T, TL>& v, double* red) {
+// residuals summed per thread in cell order, then over the workgroup.
+template <typename T, typename TL>
+__device__ __forceinline__ double tail_resnorm(const TailView<T, TL>& v, double* red) {
   const Geom& g = v.g;
   const int ncell = (int)g.n;
   const float rnx = 1.0f / (float)g.nx, rny = 1.0f / (float)g.ny;
   double s2 = 0.0;
-  for (int q = threadIdx.x; q < ncell; q += STRIDE) {
+  for (int q = threadIdx.x; q < ncell; q += kTailThreads) {
     bool act;
     const T r = tail_cell_residual<T, TL>(v, q, rnx, rny, act);
     if (act) s2 += (double)r * (double)r;
   }
-  return sqrt(grp_sum<STRIDE>(s2, red));
+  return sqrt(grp_sum<kTailThreads>(s2, red));
 }
 
 // sigma -= its mean over the active cells (FP64 sum and mean, the
@@ -348,206 +335,354 @@ __device__ __forceinline__ void grp_project(const TailView<T, TL>& v, double* re
   grp_sync<STRIDE>();
 }
 
-// Smoothing of the coarsest level by one group: nu_coarse sweeps, or with
-// coarse_rtol > 0 the right-hand side projected to zero mean, then sweeps in
-// groups of max(1, nu_coarse), the residual norm checked after each, until
-// it is at most coarse_rtol times its value on entry or coarse_max sweeps
-// are done (the last group cut to fit).  Returns the number of sweeps.
-template <typename T, typename TL, int STRIDE>
-__device__ __forceinline__ int grp_coarsest(const TailView<T, TL>& v, int nu_coarse,
-                                            double coarse_rtol, int coarse_max, T omega,
-                                            double* red) {
-  int n = 0;
+// Smoothing of the coarsest level by the workgroup from LDS or global memory,
+// for levels too large for registers: nu_coarse sweeps, or with coarse_rtol >
+// 0 the right-hand side projected to zero mean, then sweeps in groups of
+// max(1, nu_coarse), the residual norm checked after each, until it is at most
+// coarse_rtol times its value on entry or coarse_max sweeps are done (the last
+// group cut to fit).  Returns the number of sweeps.
+template <typename T, typename TL>
+__device__ __forceinline__ int plain_coarsest(const TailView<T, TL>& v, int nu_coarse,
+                                              double coarse_rtol, int coarse_max, T omega,
+                                              double* red) {
   if (!(coarse_rtol > 0.0)) {
-    for (; n < nu_coarse; ++n) {
-      grp_half_sweep<T, TL, STRIDE>(v, 0, omega);
-      grp_half_sweep<T, TL, STRIDE>(v, 1, omega);
-    }
-    return n;
+    tail_sweeps<T, TL>(v, nu_coarse, omega);
+    return nu_coarse;
   }
-  grp_project<T, TL, STRIDE>(v, red);
-  const double lim = coarse_rtol * grp_resnorm<T, TL, STRIDE>(v, red);
+  grp_project<T, TL, kTailThreads>(v, red);
+  const double lim = coarse_rtol * tail_resnorm<T, TL>(v, red);
   const int group = nu_coarse > 1 ? nu_coarse : 1;
+  int n = 0;
   while (n < coarse_max) {
     const int k = min(group, coarse_max - n);
-    for (int s = 0; s < k; ++s) {
-      grp_half_sweep<T, TL, STRIDE>(v, 0, omega);
-      grp_half_sweep<T, TL, STRIDE>(v, 1, omega);
-    }
+    tail_sweeps<T, TL>(v, k, omega);
     n += k;
-    if (n < coarse_max && grp_resnorm<T, TL, STRIDE>(v, red) <= lim) break;
+    if (n < coarse_max && tail_resnorm<T, TL>(v, red) <= lim) break;
   }
   return n;
 }
 
-// Register-resident variant for the first wavefront on a level of at most
-// 2 x 64 x-pairs: each lane owns up to two x-pairs, i.e. two cells of each
-// colour, and keeps their indices, neighbour indices, faces and sigma in
-// registers for the whole coarsest smoothing; a half-sweep then reads only
-// the neighbours' x from LDS.  Every update is relax_cell on the operands
-// grp_half_sweep passes it, so the iterates are bitwise the same.
-constexpr int kRegPairs = 2 * kWave;
+// Register-resident smoothing of a level by a group of STRIDE threads, for
+// levels of at most NS x STRIDE x-pairs: each thread owns NS pairs, one cell of
+// each colour, and keeps their x, faces, sigma, diagonal and neighbour addresses
+// in registers from the first sweep to the last; x is also kept in LDS, one
+// array per colour indexed by pair, so that a half-sweep reads five neighbours
+// of the other colour at consecutive addresses (the sixth is the thread's own)
+// and writes one value.  A half-sweep is bound by instruction issue of the one
+// workgroup: working indices, wraps and faces out of LDS each time took about
+// three times as long.  Measured on a V-cycle with a 15 x 11 x 9 coarsest level:
+// tail 61 -> 27 us; on the tails of a batch of 64 problems 111 -> 34 us.  Every
+// update rounds as relax_cell on the same operands, so the iterates are
+// bitwise those of the plain half-sweeps.
+constexpr int kRegPairsWave = 2 * kWave;        // pairs one wavefront takes
+constexpr int kRegSlots = 2;                    // most pairs of a workgroup's thread
+constexpr int kRegPad = 4;                      // the zero read beyond a wall, and padding
+constexpr int kRegPairs = kRegSlots * kTailThreads;
+__host__ __device__ constexpr int reg_colour(int slots, int stride) {  // elements of one colour
+  return slots * stride + kRegPad;
+}
 
 template <typename T>
-struct RegCell {
-  int q;       // cell index, -1: none
-  int nb[6];   // x+1, x-1, y+1, y-1, z+1, z-1 (wrapped where periodic)
-  int in;      // bit d: neighbour d is in the grid (or wrapped)
-  T f[6];      // faces: low x, high x, low y, high y, low z, high z (0 beyond a wall)
-  T sg;
+using LdsPtr = __attribute__((address_space(3))) T*;
+
+template <typename T>
+struct TailPair {
+  LdsPtr<T> own;                // colour 0's entry of this pair
+  LdsPtr<const T> n, s, t, b;   // colour 0's entries of the y and z neighbours
+  LdsPtr<const T> ext[2];       // by colour: the x neighbour in another pair
+  T f[2][6];                    // by colour: low x, high x, low y, high y, low z, high z
+  T sg[2], rd[2], x[2];         // rd: FP32 1 / D as relax_cell takes it, FP64 D
+  int q;                        // the pair's first cell, -1: none
+  bool first;                   // the first cell of the pair has colour 0
+  bool two;                     // the pair has a second cell
+  bool on[2];                   // by colour: the cell exists and D != 0
 };
 
-template <typename T, typename TL>
-__device__ __forceinline__ RegCell<T> reg_cell(const TailView<T, TL>& v, int p, int colour) {
-  const Geom& g = v.g;
-  const int nx = g.nx, ny = g.ny;
-  const int sy = nx, sz = nx * ny, n = sz * g.nz;
-  const int pr = (nx + 1) >> 1;
-  RegCell<T> c;
-  c.q = -1;
-  if (p >= pr * ny * g.nz) return c;
-  const int row = tail_div(p, pr, 1.0f / (float)pr);
-  const int m = p - row * pr;
-  const int k = tail_div(row, ny, 1.0f / (float)ny);
-  const int j = row - k * ny;
-  const int i = 2 * m + ((j + k + colour) & 1);
-  if (i >= nx) return c;
-  const int q = row * nx + i;
-  c.q = q;
-  const bool ok[6] = {i + 1 < nx || (bool)g.px, i > 0 || (bool)g.px,
-                      j + 1 < ny || (bool)g.py, j > 0 || (bool)g.py,
-                      k + 1 < g.nz || (bool)g.pz, k > 0 || (bool)g.pz};
-  c.nb[0] = (i + 1 < nx) ? q + 1 : q - (nx - 1);
-  c.nb[1] = (i > 0) ? q - 1 : q + (nx - 1);
-  c.nb[2] = (j + 1 < ny) ? q + sy : q - (ny - 1) * sy;
-  c.nb[3] = (j > 0) ? q - sy : q + (ny - 1) * sy;
-  c.nb[4] = (k + 1 < g.nz) ? q + sz : q - (g.nz - 1) * sz;
-  c.nb[5] = (k > 0) ? q - sz : q + (g.nz - 1) * sz;
-  c.in = 0;
+template <typename T, typename TL, int NS, int STRIDE>
+struct TailRegs {
+  static constexpr int CS = reg_colour(NS, STRIDE);
+  TailPair<T> a[NS];
+
+  // Takes the level's x (with the prolonged correction x += P x_c on active
+  // cells if PROL), faces and sigma; x's place in LDS (xs) may be v.x itself.
+  template <bool PROL>
+  __device__ __forceinline__ void load(const TailView<T, TL>& v, T* xs,
+                                       const TailLevel<T, TL>* fl, const TailView<T, TL>* cv) {
+    const Geom& g = v.g;
+    const int nx = g.nx, ny = g.ny, nz = g.nz;
+    const int sy = nx, sz = nx * ny, n = sz * nz;
+    const int pr = (nx + 1) >> 1, pz = pr * ny;
+    const float rpr = 1.0f / (float)pr, rny = 1.0f / (float)ny;
+    const LdsPtr<T> c0 = (LdsPtr<T>)xs;
+    const LdsPtr<const T> zero = c0 + (CS - 1);
 #pragma unroll
-  for (int d = 0; d < 6; ++d) c.in |= ok[d] ? (1 << d) : 0;
-  c.f[0] = ldL<T>(v.L, q);
-  c.f[1] = ok[0] ? ldL<T>(v.L, c.nb[0]) : T(0);
-  c.f[2] = ldL<T>(v.L + n, q);
-  c.f[3] = ok[2] ? ldL<T>(v.L + n, c.nb[2]) : T(0);
-  c.f[4] = ldL<T>(v.L + 2 * n, q);
-  c.f[5] = ok[4] ? ldL<T>(v.L + 2 * n, c.nb[4]) : T(0);
-  c.sg = T(0);
-  return c;
-}
-
-// The six neighbour values of a cell (0 outside a wall) into nv.
-template <typename T>
-__device__ __forceinline__ void reg_nbrs(const T* x, const RegCell<T>& c, T (&nv)[6]) {
+    for (int it = 0; it < NS; ++it) {
+      TailPair<T>& P = a[it];
+      const int p = threadIdx.x + it * STRIDE;
+      P.q = -1;
+      P.two = false;
+      P.first = true;
+      P.own = c0 + p;
+      P.n = P.s = P.t = P.b = P.ext[0] = P.ext[1] = zero;
 #pragma unroll
-  for (int d = 0; d < 6; ++d) nv[d] = ((c.in >> d) & 1) ? x[c.nb[d]] : T(0);
-}
+      for (int c = 0; c < 2; ++c) {
+        P.on[c] = false;
+        P.x[c] = P.sg[c] = P.rd[c] = T(0);
+#pragma unroll
+        for (int d = 0; d < 6; ++d) P.f[c][d] = T(0);
+      }
+      if (p >= pz * nz) continue;
+      const int row = tail_div(p, pr, rpr);
+      const int m = p - row * pr;
+      const int k = tail_div(row, ny, rny);
+      const int j = row - k * ny;
+      P.q = row * nx + 2 * m;
+      P.two = 2 * m + 1 < nx;
+      P.first = ((j + k) & 1) == 0;
+      // neighbours in the pair grid (periodic sizes are even); beyond a wall the zero
+      const bool ny_in = j + 1 < ny || g.py, sy_in = j > 0 || g.py;
+      const bool tz_in = k + 1 < nz || g.pz, bz_in = k > 0 || g.pz;
+      if (ny_in) P.n = P.own + (j + 1 < ny ? pr : -(ny - 1) * pr);
+      if (sy_in) P.s = P.own + (j > 0 ? -pr : (ny - 1) * pr);
+      if (tz_in) P.t = P.own + (k + 1 < nz ? pz : -(nz - 1) * pz);
+      if (bz_in) P.b = P.own + (k > 0 ? -pz : (nz - 1) * pz);
+#pragma unroll
+      for (int c = 0; c < 2; ++c) {
+        const bool lo = P.first == (c == 0);  // the pair's first cell
+        if (!lo && !P.two) continue;
+        const int i = 2 * m + (lo ? 0 : 1);
+        const int q = row * nx + i;
+        const bool e_in = i + 1 < nx || g.px, w_in = i > 0 || g.px;
+        if (lo && w_in) P.ext[c] = P.own + (m > 0 ? -1 : pr - 1);
+        if (!lo && e_in) P.ext[c] = P.own + (m + 1 < pr ? 1 : -(pr - 1));
+        const int qe = (i + 1 < nx) ? q + 1 : q - (nx - 1);
+        const int qn = (j + 1 < ny) ? q + sy : q - (ny - 1) * sy;
+        const int qt = (k + 1 < nz) ? q + sz : q - (nz - 1) * sz;
+        T* f = P.f[c];
+        f[0] = ldL<T>(v.L, q);
+        f[1] = e_in ? ldL<T>(v.L, qe) : T(0);
+        f[2] = ldL<T>(v.L + n, q);
+        f[3] = ny_in ? ldL<T>(v.L + n, qn) : T(0);
+        f[4] = ldL<T>(v.L + 2 * n, q);
+        f[5] = tz_in ? ldL<T>(v.L + 2 * n, qt) : T(0);
+        const T s = ((f[0] + f[1]) + (f[2] + f[3])) + (f[4] + f[5]);
+        P.on[c] = !(s == T(0));
+        if constexpr (sizeof(T) == 4)
+          P.rd[c] = __builtin_amdgcn_rcpf(-s);
+        else
+          P.rd[c] = -s;
+        P.sg[c] = v.s[q];
+        P.x[c] = v.x[q];
+        if constexpr (PROL)
+          if (v.a[q])
+            P.x[c] += cv->x[(k >> (fl->cz >> 1)) * (int)cv->g.sz +
+                            (j >> (fl->cy >> 1)) * (int)cv->g.sy + (i >> (fl->cx >> 1))];
+      }
+    }
+    grp_sync<STRIDE>();  // v.x is read before its place is used
+#pragma unroll
+    for (int it = 0; it < NS; ++it) {
+      a[it].own[0] = a[it].x[0];
+      a[it].own[CS] = a[it].x[1];
+    }
+    if (threadIdx.x == 0) c0[CS - 1] = c0[2 * CS - 1] = T(0);
+    grp_sync<STRIDE>();
+  }
 
-template <typename T>
-__device__ __forceinline__ void reg_relax(T* x, const RegCell<T>& c, T omega) {
-  if (c.q < 0) return;
-  T nv[6];
-  reg_nbrs<T>(x, c, nv);
-  x[c.q] = relax_cell<T>(x[c.q], nv[0], nv[1], nv[2], nv[3], nv[4], nv[5], c.f[0], c.f[1],
-                         c.f[2], c.f[3], c.f[4], c.f[5], c.sg, omega);
-}
+  // A x of the pair's cell of colour c, summed as relax_cell and stencil_Ax do.
+  __device__ __forceinline__ static T flux(const TailPair<T>& P, int c) {
+    const int o = (1 - c) * CS;
+    const T xc = P.x[c];
+    const bool lo = P.first == (c == 0);
+    const T ex = P.ext[c][o], in = P.x[1 - c];
+    const T xe = lo ? in : ex, xw = lo ? ex : in;
+    T ax = T(0);
+    ax += P.f[c][1] * (xe - xc);
+    ax += P.f[c][0] * (xw - xc);
+    ax += P.f[c][3] * (P.n[o] - xc);
+    ax += P.f[c][2] * (P.s[o] - xc);
+    ax += P.f[c][5] * (P.t[o] - xc);
+    ax += P.f[c][4] * (P.b[o] - xc);
+    return ax;
+  }
 
-// Squared residual sigma - A x of an owned active cell (0 otherwise).
-template <typename T>
-__device__ __forceinline__ double reg_res2(const T* x, const RegCell<T>& c) {
-  if (c.q < 0) return 0.0;
-  T nv[6];
-  reg_nbrs<T>(x, c, nv);
-  const T xc = x[c.q];
-  T ax = T(0), d = T(0);
-  ax += c.f[1] * (nv[0] - xc);
-  ax += c.f[0] * (nv[1] - xc);
-  d += c.f[0] + c.f[1];
-  ax += c.f[3] * (nv[2] - xc);
-  ax += c.f[2] * (nv[3] - xc);
-  d += c.f[2] + c.f[3];
-  ax += c.f[5] * (nv[4] - xc);
-  ax += c.f[4] * (nv[5] - xc);
-  d += c.f[4] + c.f[5];
-  if (-d == T(0)) return 0.0;
-  const T r = c.sg - ax;
-  return (double)r * (double)r;
-}
+  __device__ __forceinline__ void sweep(T omega) {
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+#pragma unroll
+      for (int it = 0; it < NS; ++it) {
+        TailPair<T>& P = a[it];
+        if (!P.on[c]) continue;
+        const T ax = flux(P, c);
+        if constexpr (sizeof(T) == 4)
+          P.x[c] = P.x[c] + omega * (P.sg[c] - ax) * P.rd[c];
+        else
+          P.x[c] = P.x[c] + omega * (P.sg[c] - ax) / P.rd[c];
+        P.own[c * CS] = P.x[c];
+      }
+      grp_sync<STRIDE>();
+    }
+  }
 
-template <typename T, typename TL>
-__device__ __forceinline__ int reg_coarsest(const TailView<T, TL>& v, int nu_coarse,
+  // ||sigma - A x||_2 over the active cells, the same in every thread; FP64
+  // squares of the dtype residuals in a fixed order.  red: STRIDE / 64 doubles,
+  // not read again until a sweep has passed.
+  __device__ __forceinline__ double norm(double* red) const {
+    double s2 = 0.0;
+#pragma unroll
+    for (int c = 0; c < 2; ++c)
+#pragma unroll
+      for (int it = 0; it < NS; ++it)
+        if (a[it].on[c]) {
+          const T r = a[it].sg[c] - flux(a[it], c);
+          s2 += (double)r * (double)r;
+        }
+    s2 = wave_sum_rows(s2);
+    if constexpr (STRIDE > kWave) {
+      if ((threadIdx.x & (kWave - 1)) == 0) red[threadIdx.x / kWave] = s2;
+      __syncthreads();
+      s2 = 0.0;
+#pragma unroll
+      for (int w = 0; w < STRIDE / kWave; ++w) s2 += red[w];
+    }
+    return sqrt(s2);
+  }
+
+  // Puts val(pair, colour) of every cell in its place in the level's x.
+  template <typename F>
+  __device__ __forceinline__ void put(T* x, F&& val) const {
+#pragma unroll
+    for (int it = 0; it < NS; ++it) {
+      const TailPair<T>& P = a[it];
+      if (P.q < 0) continue;
+      const T v0 = val(P, 0), v1 = val(P, 1);
+      x[P.q] = P.first ? v0 : v1;
+      if (P.two) x[P.q + 1] = P.first ? v1 : v0;
+    }
+  }
+  __device__ __forceinline__ void store(const TailView<T, TL>& v) const {
+    put(v.x, [](const TailPair<T>& P, int c) { return P.x[c]; });
+    grp_sync<STRIDE>();
+  }
+};
+
+// The coarsest level's smoothing (see plain_coarsest) from registers.
+template <typename T, typename TL, int NS, int STRIDE>
+__device__ __forceinline__ int reg_coarsest(const TailView<T, TL>& v, T* xs, int nu_coarse,
                                             double coarse_rtol, int coarse_max, T omega,
                                             double* red) {
-  const int lane = threadIdx.x;
-  RegCell<T> c[2][2];  // [colour][x-pair slot]
-#pragma unroll
-  for (int col = 0; col < 2; ++col)
-#pragma unroll
-    for (int it = 0; it < 2; ++it) c[col][it] = reg_cell<T, TL>(v, lane + kWave * it, col);
-  const bool rule = coarse_rtol > 0.0;
-  if (rule) grp_project<T, TL, kWave>(v, red);
-#pragma unroll
-  for (int col = 0; col < 2; ++col)
-#pragma unroll
-    for (int it = 0; it < 2; ++it)
-      if (c[col][it].q >= 0) c[col][it].sg = v.s[c[col][it].q];
-  auto sweep = [&]() {
-#pragma unroll
-    for (int col = 0; col < 2; ++col) {
-      reg_relax<T>(v.x, c[col][0], omega);
-      reg_relax<T>(v.x, c[col][1], omega);
-      wave_sync();
-    }
-  };
-  auto norm = [&]() {
-    double a = 0.0;
-#pragma unroll
-    for (int col = 0; col < 2; ++col)
-#pragma unroll
-      for (int it = 0; it < 2; ++it) a += reg_res2<T>(v.x, c[col][it]);
-    return sqrt(wave_sum(a));
-  };
+  TailRegs<T, TL, NS, STRIDE> r;
+  r.template load<false>(v, xs, nullptr, nullptr);
   int n = 0;
-  if (!rule) {
-    for (; n < nu_coarse; ++n) sweep();
-    return n;
+  if (!(coarse_rtol > 0.0)) {
+    for (; n < nu_coarse; ++n) r.sweep(omega);
+  } else {
+    const double lim = coarse_rtol * r.norm(red);
+    const int group = nu_coarse > 1 ? nu_coarse : 1;
+    while (n < coarse_max) {
+      const int k = min(group, coarse_max - n);
+      for (int s = 0; s < k; ++s) r.sweep(omega);
+      n += k;
+      if (n < coarse_max && r.norm(red) <= lim) break;
+    }
   }
-  const double lim = coarse_rtol * norm();
-  const int group = nu_coarse > 1 ? nu_coarse : 1;
-  while (n < coarse_max) {
-    const int k = min(group, coarse_max - n);
-    for (int s2 = 0; s2 < k; ++s2) sweep();
-    n += k;
-    if (n < coarse_max && norm() <= lim) break;
-  }
+  r.store(v);
   return n;
 }
 
-// The coarsest level's smoothing (grp_coarsest) by the first wavefront or
-// the workgroup; returns the number of sweeps to every thread.
+// The coarsest level's smoothing by the first wavefront or the workgroup;
+// returns the number of sweeps to every thread.
 template <typename T, typename TL>
-__device__ __forceinline__ int tail_coarsest(const TailView<T, TL>& v, int nu_coarse,
-                                             double coarse_rtol, int coarse_max, T omega,
-                                             int* count) {
-  __shared__ double red;
+__device__ __forceinline__ int tail_coarsest(const TailView<T, TL>& v, T* xs, int reg,
+                                             int nu_coarse, double coarse_rtol, int coarse_max,
+                                             T omega, int* count) {
+  __shared__ double red[kTailThreads / kWave];
   const int pairs = ((v.g.nx + 1) >> 1) * v.g.ny * v.g.nz;
-  if (pairs <= kRegPairs) {
-    if (threadIdx.x < kWave) {
-      const int n = reg_coarsest<T, TL>(v, nu_coarse, coarse_rtol, coarse_max, omega, &red);
-      if (threadIdx.x == 0) *count = n;
+  const bool one_wave = pairs <= kRegPairsWave || v.g.n <= kWaveCells;
+  if (reg > 0) {
+    if (coarse_rtol > 0.0) {
+      if (one_wave) {
+        if (threadIdx.x < kWave) grp_project<T, TL, kWave>(v, red);
+        __syncthreads();
+      } else {
+        grp_project<T, TL, kTailThreads>(v, red);
+      }
     }
-  } else if (v.g.n <= kWaveCells) {
-    if (threadIdx.x < kWave) {
-      const int n = grp_coarsest<T, TL, kWave>(v, nu_coarse, coarse_rtol, coarse_max, omega, &red);
-      if (threadIdx.x == 0) *count = n;
+    int n = 0;
+    if (pairs <= kRegPairsWave) {
+      if (threadIdx.x < kWave)
+        n = reg_coarsest<T, TL, kRegPairsWave / kWave, kWave>(v, xs, nu_coarse, coarse_rtol,
+                                                              coarse_max, omega, red);
+    } else if (reg == 1) {
+      n = reg_coarsest<T, TL, 1, kTailThreads>(v, xs, nu_coarse, coarse_rtol, coarse_max, omega,
+                                               red);
+    } else {
+      n = reg_coarsest<T, TL, 2, kTailThreads>(v, xs, nu_coarse, coarse_rtol, coarse_max, omega,
+                                               red);
     }
+    if (threadIdx.x == 0) *count = n;
   } else {
     const int n =
-        grp_coarsest<T, TL, kTailThreads>(v, nu_coarse, coarse_rtol, coarse_max, omega, &red);
+        plain_coarsest<T, TL>(v, nu_coarse, coarse_rtol, coarse_max, omega, red);
     if (threadIdx.x == 0) *count = n;
   }
   __syncthreads();
   return *count;
+}
+
+// Pre-smoothing and restriction of a level from registers: the residuals take
+// x's place while the coarse cells sum them, in the order of tail_restrict.
+template <typename T, typename TL, int NS>
+__device__ __forceinline__ void reg_down(const TailView<T, TL>& f, T* xs,
+                                         const TailLevel<T, TL>& fl, const TailView<T, TL>& c,
+                                         int nsw, T omega) {
+  TailRegs<T, TL, NS, kTailThreads> r;
+  r.template load<false>(f, xs, nullptr, nullptr);
+  for (int s = 0; s < nsw; ++s) r.sweep(omega);
+  T res[NS][2];
+#pragma unroll
+  for (int it = 0; it < NS; ++it)
+#pragma unroll
+    for (int col = 0; col < 2; ++col)
+      res[it][col] = r.a[it].on[col] ? r.a[it].sg[col] - r.flux(r.a[it], col) : T(0);
+  __syncthreads();
+  r.put(f.x, [&](const TailPair<T>& P, int col) { return res[&P - r.a][col]; });
+  __syncthreads();
+  const Geom& gc = c.g;
+  const int sy = f.g.nx, sz = f.g.nx * f.g.ny;
+  const float rnx = 1.0f / (float)gc.nx, rny = 1.0f / (float)gc.ny;
+  for (int q = threadIdx.x; q < (int)gc.n; q += kTailThreads) {
+    const int row = tail_div(q, gc.nx, rnx);
+    const int I = q - row * gc.nx;
+    const int K = tail_div(row, gc.ny, rny);
+    const int J = row - K * gc.ny;
+    auto column = [&](int i, int j) {
+      T acc = T(0);
+      for (int dz = 0; dz < fl.cz; ++dz) acc += f.x[(K * fl.cz + dz) * sz + j * sy + i];
+      return acc;
+    };
+    T rr[2];
+    for (int dy = 0; dy < fl.cy; ++dy) {
+      const int j = J * fl.cy + dy;
+      T acc = column(I * fl.cx, j);
+      if (fl.cx == 2) acc += column(I * fl.cx + 1, j);
+      rr[dy] = acc;
+    }
+    c.s[q] = (fl.cy == 2) ? rr[0] + rr[1] : rr[0];
+    c.x[q] = T(0);
+  }
+  __syncthreads();
+  r.store(f);
+}
+
+// Correction and post-smoothing of a level from registers.
+template <typename T, typename TL, int NS>
+__device__ __forceinline__ void reg_up(const TailView<T, TL>& f, T* xs, const TailLevel<T, TL>& fl,
+                                       const TailView<T, TL>& c, int nsw, T omega) {
+  TailRegs<T, TL, NS, kTailThreads> r;
+  r.template load<true>(f, xs, &fl, &c);
+  for (int s = 0; s < nsw; ++s) r.sweep(omega);
+  r.store(f);
 }
 
 // Copy n elements between global memory and LDS in 16-byte pieces, several
@@ -598,16 +733,33 @@ __device__ __forceinline__ void tail_run(const TailArgs<T, TL>& a, char* tail_ld
   }
   for (int l = 0; l < last; ++l) {
     const TailView<T, TL> f = tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l]);
-    tail_sweeps<T, TL>(f, a.nu_pre, omega);
-    tail_restrict<T, TL>(f, a.lv[l], tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l + 1]));
+    const TailView<T, TL> c = tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l + 1]);
+    T* const xs = (T*)(tail_lds + a.lv[l].ox);
+    if (a.lv[l].reg == 1) {
+      reg_down<T, TL, 1>(f, xs, a.lv[l], c, a.nu_pre, omega);
+    } else if (a.lv[l].reg == 2) {
+      reg_down<T, TL, 2>(f, xs, a.lv[l], c, a.nu_pre, omega);
+    } else {
+      tail_sweeps<T, TL>(f, a.nu_pre, omega);
+      tail_restrict<T, TL>(f, a.lv[l], c);
+    }
   }
   const int nc = tail_coarsest<T, TL>(tail_view<T, TL, GLOBAL>(tail_lds, a.lv[last]),
-                                      a.nu_coarse, a.coarse_rtol, a.coarse_max, omega, &count);
+                                      (T*)(tail_lds + a.lv[last].ox), a.lv[last].reg, a.nu_coarse,
+                                      a.coarse_rtol, a.coarse_max, omega, &count);
   if (a.sweeps && threadIdx.x == 0) *a.sweeps = nc;
   for (int l = last - 1; l >= 0; --l) {
     const TailView<T, TL> f = tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l]);
-    tail_prolong<T, TL>(f, a.lv[l], tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l + 1]));
-    tail_sweeps<T, TL>(f, a.nu_post, omega);
+    const TailView<T, TL> c = tail_view<T, TL, GLOBAL>(tail_lds, a.lv[l + 1]);
+    T* const xs = (T*)(tail_lds + a.lv[l].ox);
+    if (a.lv[l].reg == 1) {
+      reg_up<T, TL, 1>(f, xs, a.lv[l], c, a.nu_post, omega);
+    } else if (a.lv[l].reg == 2) {
+      reg_up<T, TL, 2>(f, xs, a.lv[l], c, a.nu_post, omega);
+    } else {
+      tail_prolong<T, TL>(f, a.lv[l], c);
+      tail_sweeps<T, TL>(f, a.nu_post, omega);
+    }
   }
   if constexpr (!GLOBAL) {
     for (int l = 0; l < a.nl; ++l) {
