@@ -9,8 +9,8 @@
 // memory latency), does the four half-sweeps in place in LDS, each one cell
 // ring narrower than the one before (a colour's cells depend only on the
 // other colour), and stores the cube.  The halo is recomputed by neighbouring
-// cubes: 8 times the cells, which costs less than the march on levels of up to
-// kCubeCells cells (measured there).
+// cubes: 8 times the cells, which costs less than the march on levels of few
+// cubes (cube_level has the measurements).
 //
 // A thread owns an x-pair column of four planes: x lives in LDS, sigma and the
 // faces of its eight cells in registers.  Cells outside a wall hold zeros

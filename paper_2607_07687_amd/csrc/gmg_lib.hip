@@ -867,20 +867,27 @@ bool pair_capable(const gmg_params& p, const Geom& g) {
 }
 
 // Whether a level's consecutive sweeps run on LDS cubes (gmg_cube.h) by
-// default: small levels, where a launch's latency counts and not the halo each
-// cube recomputes.  Two sweeps from Python, us, cubes against the two-sweep
-// pass (FP32) or two fused sweeps (FP64, odd nx):
-//   32^3      FP32 10.2 / 16.1   FP64 11.2 / 23.7
-//   64^3           14.5 / 17.4        21.3 / 26.4
-//   96x64x64       20.2 / 18.0        29.3 / 34.1
-//   104x72x56      22.1 / 17.9        38.4 / 34.9
-//   33x47x51       12.7 / 24.5        14.3 / 31.6
-//   75x81x101      41.6 / 40.7        58.9 / 68.3
-constexpr long long kCubeCellsPair = 5LL << 16, kCubeCells = 6LL << 16, kCubeCellsOdd = 1LL << 19;
+// default: levels of few cubes, where a launch's latency counts and not the
+// halo each cube recomputes; a CU holds two cubes (FP32) at a time.  Two sweeps
+// from Python, us, cubes against what else the level would run:
+//   against the two-sweep pass    24x24x400   450 cubes  12.8 / 18.8
+//   (FP32, even nx)               64x64x64    512        14.6 / 18.3
+//                                 80x64x64    640        20.8 / 19.2
+//   against two fused sweeps      96x64x64    768        29.9 / 36.6
+//   (FP64, even nx)               104x72x56   819        38.0 / 34.8
+//                                 32x128x128  1024       37.2 / 49.9
+//                                 256x64x32   1024       42.2 / 34.5
+//   (odd nx) FP32                 25x200x90   1200       32.1 / 40.0
+//                                 33x77x201   1300       37.0 / 40.3
+//                                 75x81x101   1430       41.8 / 40.5
+//            FP64                 33x77x201   1300       56.4 / 67.7
+//                                 79x245x33   1550       67.9 / 68.1
+constexpr long long kCubesPair = 512, kCubesEven = 768, kCubesOdd = 1300;
 bool cube_level(const gmg_params& p, const Geom& g) {
-  const long long most = g.nx % 2 ? kCubeCellsOdd
-                                  : (pair_capable(p, g) ? kCubeCellsPair : kCubeCells);
-  return p.pair_sweeps && p.smoother == GMG_SMOOTH_RBGS && g.n <= most;
+  if (!p.pair_sweeps || p.smoother != GMG_SMOOTH_RBGS) return false;
+  const auto edge = [](int n) { return (n + CU_B - 1LL) / CU_B; };
+  const long long most = g.nx % 2 ? kCubesOdd : (pair_capable(p, g) ? kCubesPair : kCubesEven);
+  return edge(g.nx) * edge(g.ny) * edge(g.nz) <= most;
 }
 
 // z-chunk of the two-sweep pass: one workgroup per CU (its register
