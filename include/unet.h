@@ -89,14 +89,17 @@ size_t unet_wgrad_workspace(unet_shape s, int32_t cin, int32_t cout, int32_t tap
 unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps, float* dw,
                             float* db, void* ws, void* stream);
 
-/* Which weight-gradient kernel unet_conv_wgrad runs for these sizes (host
- * only, no GPU call): info[0] = 1 for the row-tiled kernel (3x3x3 taps, w a
- * multiple of 32 or w = 16, h a multiple of 4, 8 or a multiple of 16 input
- * channels) else 0 for the voxel-chunk kernel; info[1..3] = input channels,
- * output channels and w extent of one row-kernel workgroup (0 otherwise);
- * info[4] = number of voxel chunks (partial rows); info[5] = d planes per
- * chunk (row kernel).  info: 6 int32 written by the call.  UNET_EINVAL for a
- * bad shape, channel count or taps. */
+/* Size class and partial rows of a weight gradient (host only, no GPU call):
+ * info[0] = 1 for regular grids (3x3x3 taps, w a multiple of 32 or w = 16, h a
+ * multiple of 4, 8 or a multiple of 16 input channels), which take any multiple
+ * of 16 output channels, else 0 (16, 32, 64 or 128); info[1..3] = input
+ * channels, output channels and w extent of a chunk's part (class 1, 0
+ * otherwise); info[4] = number of chunks (partial rows of the workspace);
+ * info[5] = d planes per chunk (class 1).  3x3x3 taps on 8 or a multiple of 16
+ * input channels run the tiled kernel in both classes, which divides the grid
+ * in its own way and writes at most that many rows; the rest (and h * w * ld of
+ * 2^30 and more, or 2^31 voxels) runs the voxel-chunk kernel.  info: 6 int32
+ * written by the call.  UNET_EINVAL for a bad shape, channel count or taps. */
 unet_status unet_wgrad_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
                               int32_t* info);
 

@@ -21,6 +21,7 @@
 
 #include "../../include/unet.h"
 #include "unet_conv.h"
+#include "unet_wgrad.h"
 #include "unet_device.h"
 
 using namespace unet;
@@ -314,287 +315,38 @@ __global__ __launch_bounds__(256) void k_bias_partial(unet_shape s, const uint16
   }
 }
 
-// out[i] = sum over c of ws[c * n + i] (i < n), in two levels when there are
-// more than 64 chunks: workgroup (64 outputs, group g) sums chunks
-// [64 g, 64 g + 64), each wave 16 of them in order, the four wave sums added
-// in wave order, into tmp[g * n + i]; k_sum_split then adds the groups in
-// order.  The order depends only on the chunk count: deterministic.
-__global__ __launch_bounds__(256) void k_sum_groups(const float* __restrict__ ws, long long n,
-                                                    int nchunks, float* __restrict__ tmp) {
-  __shared__ float part[4][64];
+// Sum of the nchunks rows of ws (row length n): entries below nw go to dw, the
+// rest to db.  A workgroup takes 64 entries, its wave w the rows of the w-th of
+// WAVES parts in order, and the waves' sums are added in wave order: the order
+// depends only on the row count.  Several loads of a wave are in flight, where
+// one thread per entry walked 64 rows one latency after another (64 rows of
+// 110848 entries: 17.5 -> 9 us; 256 rows of 6928, in two launches, 11 -> 4.8).
+// Of few rows a workgroup of 16 waves is mostly start-up (32 rows of 442496
+// entries: 16.3 us, with 4 waves 8.0).
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void k_sum_rows(const float* __restrict__ ws,
+                                                             long long n, int nchunks,
+                                                             long long nw, float* __restrict__ dw,
+                                                             float* __restrict__ db) {
+  __shared__ float part[WAVES][64];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const long long i = (long long)blockIdx.x * 64 + lane;
-  const int c0 = blockIdx.y * 64 + wave * 16, c1 = min(nchunks, c0 + 16);
+  const int c0 = nchunks * wave / WAVES, c1 = nchunks * (wave + 1) / WAVES;
   float acc = 0.f;
-  if (i < n)
+  if (i < n) {
+#pragma unroll 8
     for (int c = c0; c < c1; ++c) acc += ws[(long long)c * n + i];
+  }
   part[wave][lane] = acc;
   __syncthreads();
-  if (wave == 0 && i < n)
-    tmp[(long long)blockIdx.y * n + i] = ((part[0][lane] + part[1][lane]) + part[2][lane]) + part[3][lane];
-}
-
-// Sum of the nchunks rows of ws (row length n) in row order; entries below nw
-// go to dw, the rest to db.
-__global__ void k_sum_split(const float* __restrict__ ws, long long n, int nchunks, long long nw,
-                            float* __restrict__ dw, float* __restrict__ db) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  float acc = 0.f;
-  for (int c = 0; c < nchunks; ++c) acc += ws[(long long)c * n + i];
+  if (wave > 0 || i >= n) return;
+  acc = part[0][lane];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) acc += part[w][lane];
   if (i < nw)
     dw[i] = acc;
   else
     db[i - nw] = acc;
-}
-
-// ---------------------------------------------------------------------------
-// Weight gradient, row-tiled form.  Workgroup = one voxel chunk (sample n, a
-// range of d planes, a block of 4 h rows, a w segment of WS voxels) x one
-// channel part (OT outputs x CT inputs).  The workgroup walks its planes in
-// order.  Each input plane's rows h0-1 .. h0+4 (w0-1 .. w0+WS, zeros outside
-// the grid) are staged channel-major in a 3-slot LDS ring, so that the 8
-// voxels a lane feeds to the MFMA are contiguous and the three w taps of one
-// (d, h) tap row come from one 16-byte and one 4-byte LDS read, shifted by 0,
-// 1 or 2 elements in registers.  The plane's dy rows are staged the same way.
-// A unit is 32 voxels (a row of 32, or two rows of 16).  Wave q owns one
-// 16 x 16 (output, input) channel block and all 27 taps for units
-// q / P, q / P + 4 / P, ... of every plane, plus the bias sums (an MFMA
-// against ones) when its input block is the part's first and the part starts
-// at input channel 0.  Waves that share a channel block add their sums in
-// wave order at the end.  Output: the chunk's row of ws, ws[chunk * rs + ...]
-// with dW at o * 27 cin + t cin + c and the bias sums at cout * 27 cin + o.
-// The next plane's loads are issued before the current plane's MFMAs.
-// ---------------------------------------------------------------------------
-
-struct WgradRowsArgs {
-  unet_shape s;
-  const uint16_t* x;
-  int xld, xoff, cin;
-  const uint16_t* dy;
-  int dld, doff, cout;
-  int nws, nhb, nds, dper, ncp;  // w segments, 4-row blocks, d ranges, planes per range, input parts
-  long long rs;                  // ws row stride (floats)
-  float* ws;
-};
-
-__device__ __forceinline__ uint32_t pack_lo(uint32_t a, uint32_t b) {
-  return (a & 0xFFFFu) | (b << 16);
-}
-__device__ __forceinline__ uint32_t pack_hi(uint32_t a, uint32_t b) {
-  return (a >> 16) | (b & 0xFFFF0000u);
-}
-__device__ __forceinline__ bf16x8 as_bf16x8(uint32_t a, uint32_t b, uint32_t c, uint32_t d) {
-  const uint4 v = make_uint4(a, b, c, d);
-  bf16x8 r;
-  __builtin_memcpy(&r, &v, 16);
-  return r;
-}
-
-// Four voxels x 8 channels (one 16-byte load per voxel) written channel-major:
-// row e of dst (pitch elements apart) receives the 4 voxels' channel e.
-__device__ __forceinline__ void store_quad_t(uint16_t* dst, int pitch, const uint4 (&r)[4]) {
-  const uint32_t v0[4] = {r[0].x, r[0].y, r[0].z, r[0].w};
-  const uint32_t v1[4] = {r[1].x, r[1].y, r[1].z, r[1].w};
-  const uint32_t v2[4] = {r[2].x, r[2].y, r[2].z, r[2].w};
-  const uint32_t v3[4] = {r[3].x, r[3].y, r[3].z, r[3].w};
-#pragma unroll
-  for (int e2 = 0; e2 < 4; ++e2) {
-    *reinterpret_cast<uint2*>(dst + (2 * e2) * pitch) =
-        make_uint2(pack_lo(v0[e2], v1[e2]), pack_lo(v2[e2], v3[e2]));
-    *reinterpret_cast<uint2*>(dst + (2 * e2 + 1) * pitch) =
-        make_uint2(pack_hi(v0[e2], v1[e2]), pack_hi(v2[e2], v3[e2]));
-  }
-}
-
-template <int CT, int OT, int WS>
-__global__ __launch_bounds__(256, 2) void k_wgrad_rows(WgradRowsArgs a) {
-  constexpr int CTP = CT < 16 ? 16 : CT;       // staged input channels (8 padded to 16)
-  constexpr int NCB = CTP / 16;                // 16-channel input blocks
-  constexpr int P = (OT / 16) * NCB;           // channel blocks per workgroup
-  constexpr int RPW = 4 / P;                   // waves per channel block
-  constexpr int RU = 32 / WS;                  // rows per 32-voxel unit
-  constexpr int U = 4 / RU;                    // units per plane
-  constexpr int XQ = (WS + 5) / 4;             // 4-voxel groups per staged row (WS + 2)
-  constexpr int XP = WS == 32 ? 40 : 24;       // staged row pitch (elements)
-  constexpr int XO = 8 * XP + 8;               // 8-channel group stride
-  constexpr int XR = 2 * NCB * XO;             // one staged row, all channels
-  constexpr int XPL = 6 * XR;                  // one plane slot (6 rows)
-  constexpr int DP = 40, DO = 8 * DP + 8, DU = (OT / 8) * DO;
-  constexpr int NX = 6 * XQ * (CT / 8);        // x staging items per plane
-  constexpr int ND = 4 * (WS / 4) * (OT / 8);  // dy staging items per plane
-  constexpr int SM = 3 * XPL + U * DU;         // LDS elements (ring, then dy rows)
-  // the final sums pass TG taps of every wave at a time through LDS
-  constexpr int TG = 4 * 9 * 4 * 64 * 4 <= SM * 2 ? 9 : (4 * 3 * 4 * 64 * 4 <= SM * 2 ? 3 : 1);
-  static_assert(P >= 1 && P <= 4 && 4 % P == 0, "channel blocks per workgroup");
-  static_assert(NX <= 256 && ND <= 256, "one staging item per thread");
-  static_assert(4 * TG * 4 * 64 * 4 <= SM * 2, "final sums fit in LDS");
-  __shared__ __align__(16) uint16_t smem[SM];
-  uint16_t* const xs = smem;
-  uint16_t* const ds = smem + 3 * XPL;
-
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int D = a.s.d, H = a.s.h, W = a.s.w;
-  // chunks grouped per XCD: dispatch order sends block b to XCD b % 8
-  const int nchunk = gridDim.x;
-  int chunk = blockIdx.x;
-  if ((nchunk & 7) == 0) chunk = (blockIdx.x & 7) * (nchunk >> 3) + (blockIdx.x >> 3);
-  int t = chunk;
-  const int wsg = t % a.nws;
-  t /= a.nws;
-  const int hb = t % a.nhb;
-  t /= a.nhb;
-  const int dsi = t % a.nds;
-  const int n = t / a.nds;
-  const int c0 = (blockIdx.y % a.ncp) * CT, o0 = (blockIdx.y / a.ncp) * OT;
-  const int w0 = wsg * WS, h0 = hb * 4;
-  const int d0 = dsi * a.dper, d1 = min(D, d0 + a.dper);
-  const long long plane = (long long)H * W;
-  const long long nbase = (long long)n * D * plane;
-
-  // staging items: x (staged row, 8-channel group, 4-voxel group), dy (row, group, 4 voxels)
-  const bool xitem = tid < NX;
-  const int xq = tid % XQ, xoc = (tid / XQ) % (CT / 8), xrow = tid / (XQ * (CT / 8));
-  const int xh = h0 - 1 + xrow;
-  const bool xrow_ok = xitem && xh >= 0 && xh < H;
-  const bool ditem = tid < ND;
-  const int dq = tid % (WS / 4), doc = (tid / (WS / 4)) % (OT / 8), drow = tid / ((WS / 4) * (OT / 8));
-  uint4 rx[4], rd[4];
-  auto load_x = [&](int p) {
-    const bool ok = xrow_ok && p >= 0 && p < D;
-    const long long vrow = nbase + (long long)p * plane + (long long)xh * W;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int w = w0 - 1 + 4 * xq + j;
-      rx[j] = make_uint4(0, 0, 0, 0);
-      if (ok && w >= 0 && w < W && 4 * xq + j < WS + 2)
-        rx[j] = *reinterpret_cast<const uint4*>(a.x + (vrow + w) * a.xld + a.xoff + c0 + 8 * xoc);
-    }
-  };
-  auto store_x = [&](int slot) {
-    if (xitem) store_quad_t(xs + slot * XPL + xrow * XR + xoc * XO + 4 * xq, XP, rx);
-  };
-  auto load_dy = [&](int p) {
-    const long long v = nbase + (long long)p * plane + (long long)(h0 + drow) * W + w0 + 4 * dq;
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      rd[j] = make_uint4(0, 0, 0, 0);
-      if (ditem) rd[j] = *reinterpret_cast<const uint4*>(a.dy + (v + j) * a.dld + a.doff + o0 + 8 * doc);
-    }
-  };
-  auto store_dy = [&]() {
-    if (ditem) store_quad_t(ds + (drow / RU) * DU + doc * DO + (drow % RU) * WS + 4 * dq, DP, rd);
-  };
-
-  if (CT == 8) {  // padded input channels 8..15 stay zero
-    for (int i = tid; i < 3 * 6 * (XO / 8); i += 256) {
-      const int sr = i / (XO / 8), off = i % (XO / 8);
-      *reinterpret_cast<uint4*>(xs + sr * XR + XO + 8 * off) = make_uint4(0, 0, 0, 0);
-    }
-  }
-  load_x(d0 - 1);
-  store_x(0);
-  load_x(d0);
-  store_x(1);
-  load_x(d0 + 1);
-  store_x(2);
-  load_dy(d0);
-  store_dy();
-  __syncthreads();
-  if (d0 + 1 < d1) {
-    load_x(d0 + 2);
-    load_dy(d0 + 1);
-  }
-
-  const int cblk = wave % P, rsub = wave / P;
-  const int ob = cblk / NCB, cb = cblk % NCB;
-  const int g = lane >> 4, l16 = lane & 15;
-  const int oo = ob * 16 + l16;
-  const int aoff = (oo >> 3) * DO + (oo & 7) * DP + 8 * g;
-  const int ci = cb * 16 + l16;
-  const int boff = (ci >> 3) * XO + (ci & 7) * XP + (RU == 2 ? 8 * (g & 1) : 8 * g);
-  const int grow = RU == 2 ? (g >> 1) : 0;
-  const bool do_bias = cb == 0 && c0 == 0;
-  const bf16x8 ones = as_bf16x8(0x3F803F80u, 0x3F803F80u, 0x3F803F80u, 0x3F803F80u);
-  f32x4 acc[27], bacc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-  for (int i = 0; i < 27; ++i) acc[i] = f32x4{0.f, 0.f, 0.f, 0.f};
-
-  for (int d = d0; d < d1; ++d) {
-    for (int u = rsub; u < U; u += RPW) {
-      const bf16x8 av = ld8(ds + u * DU + aoff);
-      if (do_bias) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, ones, bacc, 0, 0, 0);
-      const int lr = u * RU + grow;  // row of the 4-row block
-#pragma unroll
-      for (int kd = 0; kd < 3; ++kd) {
-        const uint16_t* xb = xs + ((d + kd - d0) % 3) * XPL + boff + lr * XR;
-#pragma unroll
-        for (int kh = 0; kh < 3; ++kh) {
-          const uint16_t* pb = xb + kh * XR;
-          const uint4 q = *reinterpret_cast<const uint4*>(pb);
-          const uint32_t q4 = *reinterpret_cast<const uint32_t*>(pb + 8);
-          const int tp = 9 * kd + 3 * kh;
-          acc[tp] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(q.x, q.y, q.z, q.w),
-                                                            acc[tp], 0, 0, 0);
-          acc[tp + 1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
-              av,
-              as_bf16x8(__builtin_amdgcn_alignbit(q.y, q.x, 16), __builtin_amdgcn_alignbit(q.z, q.y, 16),
-                        __builtin_amdgcn_alignbit(q.w, q.z, 16), __builtin_amdgcn_alignbit(q4, q.w, 16)),
-              acc[tp + 1], 0, 0, 0);
-          acc[tp + 2] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(av, as_bf16x8(q.y, q.z, q.w, q4),
-                                                                acc[tp + 2], 0, 0, 0);
-        }
-      }
-    }
-    if (d + 1 < d1) {
-      __syncthreads();
-      store_x((d + 3 - d0) % 3);  // plane d + 2 replaces plane d - 1
-      store_dy();                 // plane d + 1
-      __syncthreads();
-      if (d + 2 < d1) {
-        load_x(d + 3);
-        load_dy(d + 2);
-      }
-    }
-  }
-
-  // Final sums: each wave parks TG taps of its tiles in LDS; the threads add
-  // the RPW waves of each channel block in wave order and store the chunk's
-  // row (16 consecutive input channels per lane group).
-  float* const red = reinterpret_cast<float*>(smem);
-  const int K = 27 * a.cin;
-  float* const row = a.ws + (long long)chunk * a.rs;
-#pragma unroll
-  for (int grp = 0; grp < 27 / TG; ++grp) {
-    __syncthreads();
-#pragma unroll
-    for (int i = 0; i < TG; ++i)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) red[((wave * TG + i) * 4 + e) * 64 + lane] = acc[TG * grp + i][e];
-    __syncthreads();
-    for (int idx = tid; idx < P * TG * 4 * 64; idx += 256) {
-      const int ln = idx & 63, e = (idx >> 6) & 3, i = (idx >> 8) % TG, cbk = (idx >> 8) / TG;
-      float v = 0.f;
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) v += red[(((cbk + P * rr) * TG + i) * 4 + e) * 64 + ln];
-      const int c = (cbk % NCB) * 16 + (ln & 15);
-      const int o = o0 + (cbk / NCB) * 16 + 4 * (ln >> 4) + e;
-      if (c < CT) row[(long long)o * K + (TG * grp + i) * a.cin + c0 + c] = v;
-    }
-  }
-  if (c0 == 0) {  // bias sums: blocks whose input block is the first
-    __syncthreads();
-#pragma unroll
-    for (int e = 0; e < 4; ++e) red[(wave * 4 + e) * 64 + lane] = bacc[e];
-    __syncthreads();
-    if (tid < (OT / 16) * 16) {
-      const int obk = tid >> 4, e = tid & 3, gg = (tid >> 2) & 3;
-      float v = 0.f;
-#pragma unroll
-      for (int rr = 0; rr < RPW; ++rr) v += red[((obk * NCB + P * rr) * 4 + e) * 64 + 16 * gg];
-      row[(long long)a.cout * K + o0 + obk * 16 + 4 * gg + e] = v;
-    }
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -1154,7 +906,6 @@ BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
       }
     }
   }
-  //FORCE
   return best;
 }
 
@@ -1207,34 +958,29 @@ void enq_brick(const BrickPlan& p, ConvArgs a, int cout, hipStream_t st) {
   }
 }
 
-// Groups of 64 chunk rows summed first when there are more than 64 rows.
+// Rows of workspace past the chunks' (part of the size callers allocate).
 long long sum_groups(long long nchunk) { return nchunk > 64 ? (nchunk + 63) / 64 : 0; }
 
 // Fixed-order sum of nchunk partial rows ws[c * rs + i] (i < rs): entries
-// below nw go to dw, the rest to db.  Groups of 64 rows first (into the
-// sum_groups(nchunk) rows after the partials) when there are more.
+// below nw go to dw, the rest to db.
 void enq_sum_rows(float* ws, long long nchunk, long long rs, long long nw, float* dw, float* db,
                   hipStream_t st) {
-  const float* rows = ws;
-  long long nrows = nchunk;
-  const long long ng = sum_groups(nchunk);
-  if (ng > 0) {
-    float* tmp = ws + nchunk * rs;
-    hipLaunchKernelGGL(k_sum_groups, dim3((unsigned)((rs + 63) / 64), (unsigned)ng), dim3(256), 0,
-                       st, ws, rs, (int)nchunk, tmp);
-    rows = tmp;
-    nrows = ng;
-  }
-  hipLaunchKernelGGL(k_sum_split, dim3((unsigned)((rs + 255) / 256)), dim3(256), 0, st, rows, rs,
-                     (int)nrows, nw, dw, db);
+  const dim3 grid((unsigned)((rs + 63) / 64));
+  if (nchunk < 64)
+    hipLaunchKernelGGL(k_sum_rows<4>, grid, dim3(256), 0, st, ws, rs, (int)nchunk, nw, dw, db);
+  else
+    hipLaunchKernelGGL(k_sum_rows<16>, grid, dim3(1024), 0, st, ws, rs, (int)nchunk, nw, dw, db);
 }
 
-// Launch plan of the weight gradient.  Row kernel when the grid tiles into
-// 4-row blocks of 32-voxel rows (w a multiple of 32) or row pairs (w = 16),
-// with 8 or a multiple of 16 input channels and 3x3x3 taps; otherwise the
-// voxel-chunk kernel.  Channel parts start at 32 x 32 and are halved while the
-// grid would have fewer than 512 workgroups; d ranges of at least 4 planes
+// Partial rows and size class of the weight gradient, as
+// unet_wgrad_workspace and unet_wgrad_kernel report them.  Regular grids (rows:
+// w a multiple of 32 or 16, h of 4, 8 or a multiple of 16 input channels, 3x3x3
+// taps) split into 4-row blocks of 32-voxel rows (w a multiple of 32) or row
+// pairs (w = 16).  Channel parts start at 32 x 32 and are halved while the
+// grid would have fewer than 512 of them; d ranges of at least 4 planes
 // then bring it to about 1024, while the partial rows stay within 8 Mi floats.
+// All other grids split into chunks of voxels.  The kernels write at most as
+// many rows.
 struct WgradPlan {
   bool rows;
   int ct, ot, ws, nws, nhb, nds, dper, ncp, nop;
@@ -1289,6 +1035,83 @@ WgradPlan wgrad_plan(unet_shape s, int cin, int cout, int taps) {
   }
   p.ngroup = sum_groups(p.nchunk);
   return p;
+}
+
+// Whether the tiled kernel (unet_wgrad.h) takes a weight gradient: 3x3x3 taps,
+// 8 or a multiple of 16 input channels, planes that a buffer descriptor spans
+// and voxels that an int counts.  Against the gathered voxel-chunk kernel, with
+// sums: 16 -> 16 channels on 48x56x104 37 and 211 us, 128 -> 128 on 2 x 12x20x28
+// 44 and 373, 64 -> 128 on 8x8x8 36 and 82; it is the faster one at every size.
+bool wgrad_tiled(unet_shape s, int cin, int ld, int taps) {
+  return taps == 27 && (cin == 8 || cin % 16 == 0) && (long long)s.h * s.w * ld < (1LL << 30) - 64 &&
+         nvox_of(s) < (1LL << 31);
+}
+
+// Enqueues the tiled kernel; returns the number of partial rows (at most the
+// plan's).  Its workgroups fill every CU once (a CU holds PER_CU), split over
+// the channel parts; the tile is the one that pads the grid least, then the
+// one with the smallest halo.  Channel parts of 32 unless parts of 16 leave a
+// workgroup fewer steps, six counted for its start and end: the plan's rows
+// bound the workgroups of a part (32 -> 32 channels on 24x28x52: 35 rows,
+// parts of 32 31.5 us, of 16 18.2; 32 -> 16 on 2 x 128^3: 110 and 136).
+long long enq_wgrad(unet_shape s, unet_act x, unet_act dy, const WgradPlan& p, float* ws,
+                    hipStream_t st) {
+  using namespace unet;
+  WgradArgs a{s, (const uint16_t*)x.p, x.ld, x.off, x.c, (const uint16_t*)dy.p, dy.ld, dy.off, dy.c,
+              0, 0, 0, 0, 0, 0, p.rs, ws};
+  struct Choice {
+    int ltwo, nbw, nbh, nparts, nchunk;
+    long long steps;
+    double cost;
+  };
+  auto plan = [&](auto kc) {
+    using K = decltype(kc);
+    Choice c{};
+    long long tiles = -1, halo = 0;
+    for (int two = K::TWO_HI, lg = 2; two >= K::TWO_LO; two /= 2, --lg) {
+      const int rows = K::NOC / two * K::RL;
+      const int nbw = (s.w + 8 * two - 1) / (8 * two), nbh = (s.h + rows - 1) / rows;
+      const long long nt = (long long)nbw * nbh * s.n, h = (rows + 2LL) * (8 * two + 2);
+      if (tiles >= 0 && (nt > tiles || (nt == tiles && h >= halo))) continue;
+      tiles = nt;
+      halo = h;
+      c.ltwo = lg;
+      c.nbw = nbw;
+      c.nbh = nbh;
+    }
+    c.steps = tiles * s.d;
+    c.nparts = x.c / K::CT * (dy.c / K::OT);
+    c.nchunk = (int)std::min({p.nchunk, c.steps, std::max(1LL, 256LL * K::PER_CU / c.nparts)});
+    // a second workgroup on a CU takes half its time again (measured), more than
+    // the CUs hold run in turns
+    const double per_cu = (double)c.nchunk * c.nparts / 256;
+    const double turns = per_cu <= 1 ? 1 : (per_cu <= 2 ? 0.5 + 0.5 * per_cu : per_cu * 0.75);
+    c.cost = ((c.steps + c.nchunk - 1) / c.nchunk + 6) * turns;
+    return c;
+  };
+  auto go = [&](auto kc) -> long long {
+    using K = decltype(kc);
+    const Choice c = plan(kc);
+    a.ltwo = c.ltwo;
+    a.nbw = c.nbw;
+    a.nbh = c.nbh;
+    a.ncp = x.c / K::CT;
+    a.q = (int)(c.steps / c.nchunk);
+    a.r = (int)(c.steps % c.nchunk);
+    hipLaunchKernelGGL((k_wgrad<K::CT, K::OT, K::RL, K::NT>), dim3(c.nchunk, c.nparts), dim3(K::NT),
+                       0, st, a);
+    return c.nchunk;
+  };
+  constexpr Wgrad<8, 16, 2, 512> k8{};
+  constexpr Wgrad<16, 16, 2, 512> k16{};
+  constexpr Wgrad<16, 32, 2, 512> k16w{};
+  constexpr Wgrad<32, 16, 4, 256> k32{};
+  constexpr Wgrad<32, 32, 4, 256> k32w{};
+  if (x.c == 8) return go(k8);
+  if (x.c % 32 == 0 && dy.c % 32 == 0 && plan(k32w).cost <= plan(k16).cost) return go(k32w);
+  if (x.c % 32 == 0 && dy.c % 32 && plan(k32).cost <= plan(k16).cost) return go(k32);
+  if (x.c % 32 && dy.c % 32 == 0 && plan(k16w).cost <= plan(k16).cost) return go(k16w);
+  return go(k16);
 }
 
 }  // namespace
@@ -1424,57 +1247,36 @@ unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps,
   float* wsp = (float*)ws;
   const uint16_t* xp = (const uint16_t*)x.p;
   const uint16_t* dp = (const uint16_t*)dy.p;
-  if (p.rows) {
-    WgradRowsArgs a{s, xp, x.ld, x.off, x.c, dp, dy.ld, dy.off, dy.c,
-                    p.nws, p.nhb, p.nds, p.dper, p.ncp, p.rs, wsp};
-    const dim3 grid((unsigned)p.nchunk, (unsigned)(p.ncp * p.nop));
-    const int key = p.ct * 10000 + p.ot * 100 + p.ws;
-    switch (key) {
-#define WGROWS(CT, OT, WS)                                                             \
-  case CT * 10000 + OT * 100 + WS:                                                     \
-    hipLaunchKernelGGL((k_wgrad_rows<CT, OT, WS>), grid, dim3(256), 0, st, a);         \
-    break;
-      WGROWS(8, 16, 32)
-      WGROWS(8, 32, 32)
-      WGROWS(16, 16, 32)
-      WGROWS(16, 32, 32)
-      WGROWS(32, 16, 32)
-      WGROWS(32, 32, 32)
-      WGROWS(8, 32, 16)
-      WGROWS(16, 32, 16)
-      WGROWS(32, 16, 16)
-      WGROWS(32, 32, 16)
-#undef WGROWS
-      default:
-        return ufail(UNET_EINVAL, "wgrad: no row kernel for this channel tiling");
-    }
+  const int obs = dy.c / 16;
+  if (!p.rows && obs != 1 && obs != 2 && obs != 4 && obs != 8)
+    return ufail(UNET_EINVAL, "output channels must be 16, 32, 64 or 128");
+  long long nchunk = p.nchunk;
+  if (wgrad_tiled(s, x.c, std::max(x.ld, dy.ld), taps)) {
+    nchunk = enq_wgrad(s, x, dy, p, wsp, st);
   } else {
-    const dim3 grid((K + 63) / 64, (unsigned)p.nchunk);
-    switch (dy.c / 16) {
-      case 1:
-        hipLaunchKernelGGL(k_conv_wgrad<1>, grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, dp,
-                           dy.ld, dy.off, taps, p.vchunk, p.rs, wsp);
-        break;
-      case 2:
-        hipLaunchKernelGGL(k_conv_wgrad<2>, grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, dp,
-                           dy.ld, dy.off, taps, p.vchunk, p.rs, wsp);
-        break;
-      case 4:
-        hipLaunchKernelGGL(k_conv_wgrad<4>, grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, dp,
-                           dy.ld, dy.off, taps, p.vchunk, p.rs, wsp);
-        break;
-      case 8:
-        hipLaunchKernelGGL(k_conv_wgrad<8>, grid, dim3(256), 0, st, s, xp, x.ld, x.off, x.c, dp,
-                           dy.ld, dy.off, taps, p.vchunk, p.rs, wsp);
-        break;
-      default:
-        return ufail(UNET_EINVAL, "output channels must be 16, 32, 64 or 128");
+    const long long nv = nvox_of(s);
+    const long long vchunk = p.rows ? ((nv + nchunk - 1) / nchunk + 31) / 32 * 32 : p.vchunk;
+    nchunk = (nv + vchunk - 1) / vchunk;
+    const dim3 grid((K + 63) / 64, (unsigned)nchunk);
+    auto launch = [&](auto ob) {
+      hipLaunchKernelGGL(k_conv_wgrad<decltype(ob)::value>, grid, dim3(256), 0, st, s, xp, x.ld,
+                         x.off, x.c, dp, dy.ld, dy.off, taps, vchunk, p.rs, wsp);
+    };
+    switch (obs) {
+      case 1: launch(std::integral_constant<int, 1>{}); break;
+      case 2: launch(std::integral_constant<int, 2>{}); break;
+      case 3: launch(std::integral_constant<int, 3>{}); break;
+      case 4: launch(std::integral_constant<int, 4>{}); break;
+      case 5: launch(std::integral_constant<int, 5>{}); break;
+      case 6: launch(std::integral_constant<int, 6>{}); break;
+      case 7: launch(std::integral_constant<int, 7>{}); break;
+      default: launch(std::integral_constant<int, 8>{}); break;
     }
-    hipLaunchKernelGGL(k_bias_partial, dim3((unsigned)p.nchunk), dim3(128), 0, st, s, dp, dy.ld,
-                       dy.off, dy.c, p.vchunk, p.rs, wsp + nw);
+    hipLaunchKernelGGL(k_bias_partial, dim3((unsigned)nchunk), dim3(128), 0, st, s, dp, dy.ld,
+                       dy.off, dy.c, vchunk, p.rs, wsp + nw);
   }
   UHIP(hipGetLastError());
-  enq_sum_rows(wsp, p.nchunk, p.rs, nw, dw, db, st);
+  enq_sum_rows(wsp, nchunk, p.rs, nw, dw, db, st);
   UHIP(hipGetLastError());
   return UNET_OK;
 }

@@ -145,9 +145,9 @@ def unet_conv_kernel(s, cin, cout, taps):
 
 
 def unet_wgrad_kernel(s, cin, cout, taps):
-    """Kernel choice of unet_conv_wgrad (host only): dict with rows (row-tiled
-    kernel or voxel chunks), ct / ot / ws (channels and w extent of a row
-    workgroup), chunks (partial rows) and dper (d planes per chunk)."""
+    """Size class and partial rows of unet_conv_wgrad (host only): dict with rows
+    (regular grid), ct / ot / ws (channels and w extent of a chunk's part),
+    chunks (partial rows) and dper (d planes per chunk)."""
     info = (ctypes.c_int32 * 6)()
     _check(load().unet_wgrad_kernel(s, cin, cout, taps, ctypes.cast(info, ctypes.c_void_p)))
     return {"rows": bool(info[0]), "ct": info[1], "ot": info[2], "ws": info[3],
