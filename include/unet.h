@@ -80,6 +80,12 @@ unet_status unet_conv_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t ta
 unet_status unet_conv_dgrad(unet_shape s, unet_act dy, const void* w, int32_t taps,
                             unet_act dx, void* wflip, void* stream);
 
+/* The same with the ReLU backward of dx's own layer in the same pass: dx is
+ * zero where y (its forward output, dx.c channels) is not positive, bitwise as
+ * unet_conv_dgrad followed by unet_relu_bwd. */
+unet_status unet_conv_dgrad_relu(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act y,
+                                 unet_act dx, void* wflip, void* stream);
+
 /* Weight and bias gradients: dw[o][t][c] = sum_v dy[v][o] x[v + t - 1][c],
  * db[o] = sum_v dy[v][o] (FP32 outputs, overwritten).  Deterministic split-K
  * over voxel chunks (FP32 partial rows summed in a fixed order): ws is caller
@@ -114,6 +120,11 @@ unet_status unet_pool_bwd(unet_shape fine, unet_act dy, unet_act dx, int32_t acc
                           void* stream);
 unet_status unet_up_fwd(unet_shape coarse, unet_act x, unet_act y, void* stream);
 unet_status unet_up_bwd(unet_shape coarse, unet_act dy, unet_act dx, void* stream);
+/* The same with the ReLU backward of dx's layer (forward output y) in the same
+ * pass, bitwise as the backward op followed by unet_relu_bwd on dx. */
+unet_status unet_pool_bwd_relu(unet_shape fine, unet_act dy, unet_act y, unet_act dx,
+                               int32_t accumulate, void* stream);
+unet_status unet_up_bwd_relu(unet_shape coarse, unet_act dy, unet_act y, unet_act dx, void* stream);
 
 /* 1x1x1 head to one FP32 channel: y[v] = b + sum_c w[c] x[v][c] (w, b FP32).
  * Backward: dx[v][c] = w[c] dy[v] (skipped if dx.p is NULL), dw[c] = sum_v
@@ -123,6 +134,9 @@ unet_status unet_head_fwd(unet_shape s, unet_act x, const float* w, const float*
 size_t unet_head_workspace(unet_shape s, int32_t cin);
 unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,
                           float* dw, float* db, void* ws, void* stream);
+/* The same with dx cleared where x is not positive (x is a ReLU's output). */
+unet_status unet_head_bwd_relu(unet_shape s, unet_act x, const float* w, const float* dy,
+                               unet_act dx, float* dw, float* db, void* ws, void* stream);
 
 /* Masked mean-squared error of an FP32 prediction [voxels] against target over
  * the cells with mask != 0: loss = sum (p - t)^2 / count.  Writes dpred =

@@ -20,6 +20,8 @@ struct ConvArgs {
   int groups;         // output-channel groups (workgroups that share a brick's input)
   int total;          // work items: bricks x groups
   int wide;           // y (or yf) takes 16-byte (NB = 1: 8-byte) stores
+  const uint16_t* gate;  // y is cleared where this is not positive (GATE kernels)
+  int gld, goff;
 };
 
 // Waves per SIMD that `regs` registers and about 50 more leave room for.
@@ -89,7 +91,10 @@ struct Brick {
 // LDS: the 16 lanes of a quarter wave read one 16-byte piece each of
 // consecutive voxels.  The pieces of a voxel are permuted by its column (swz):
 // a wave's read then takes 4.4 cycles (8.1 without, or permuted by col >> 2).
-template <int CK, int NC, int MB, int NB, int WD, int WC>
+// GATE: the output is the gradient of a ReLU's output and is cleared where that
+// (a.gate) is not positive; a variant of its own, since the test alone costs a
+// forward convolution 4%.
+template <int CK, int NC, int MB, int NB, int WD, int WC, bool GATE>
 __global__ __launch_bounds__(64 * WD * WC)
     __attribute__((amdgpu_waves_per_eu(Brick<CK, NC, MB, NB, WD, WC>::WAVES))) void
     k_conv_brick(ConvArgs a) {
@@ -209,8 +214,27 @@ __global__ __launch_bounds__(64 * WD * WC)
     for (int r = 0; r < NB * 4; ++r) bias[r] = a.bias ? a.bias[c + r] : 0.f;
     const int wv = t.w0 + l16, dd = t.d0 + wd;
     if (dd >= D || wv >= W) return;
-    long long o =
-        (((long long)t.n0 * D + dd) * plane + (long long)t.h0 * W + wv) * a.yld + a.yoff + c;
+    const long long vx0 = ((long long)t.n0 * D + dd) * plane + (long long)t.h0 * W + wv;
+    long long o = vx0 * a.yld + a.yoff + c;
+    uint32_t gt[GATE ? MB : 1][NB * 2];
+    if constexpr (GATE) {
+#pragma unroll
+      for (int mb = 0; mb < MB; ++mb) {
+        if (t.h0 + mb >= H) continue;
+        const uint16_t* gp = a.gate + (vx0 + (long long)mb * W) * a.gld + a.goff + c;
+        if (a.wide) {
+          if constexpr (NB == 1) {
+            const uint2 q = *reinterpret_cast<const uint2*>(gp);
+            gt[mb][0] = q.x, gt[mb][1] = q.y;
+          } else {
+            const uint4 q = *reinterpret_cast<const uint4*>(gp);
+            gt[mb][0] = q.x, gt[mb][1] = q.y, gt[mb][2] = q.z, gt[mb][3] = q.w;
+          }
+        } else {
+          for (int r = 0; r < NB * 2; ++r) gt[mb][r] = gp[2 * r] | (uint32_t)gp[2 * r + 1] << 16;
+        }
+      }
+    }
 #pragma unroll
     for (int mb = 0; mb < MB; ++mb, o += (long long)W * a.yld) {
       if (t.h0 + mb >= H) continue;
@@ -234,6 +258,9 @@ __global__ __launch_bounds__(64 * WD * WC)
 #pragma unroll
       for (int r = 0; r < NB * 2; ++r)
         h[r] = (uint32_t)f2bf(u[2 * r]) | ((uint32_t)f2bf(u[2 * r + 1]) << 16);
+      if constexpr (GATE)
+#pragma unroll
+        for (int r = 0; r < NB * 2; ++r) h[r] = gate2(h[r], gt[mb][r]);
       if (a.wide) {
         if constexpr (NB == 1)
           *reinterpret_cast<uint2*>(a.y + o) = make_uint2(h[0], h[1]);

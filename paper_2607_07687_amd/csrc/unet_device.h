@@ -19,6 +19,14 @@ __device__ __forceinline__ uint16_t f2bf(float f) {
   return (uint16_t)(u >> 16);
 }
 
+// u with the BF16 halves whose gate value is not positive (or NaN) cleared:
+// ReLU backward of a pair of gradients.
+__device__ __forceinline__ uint32_t gate2(uint32_t u, uint32_t y) {
+  const uint32_t lo = (y & 0xFFFFu) - 1u < 0x7F80u ? 0x0000FFFFu : 0u;
+  const uint32_t hi = (y >> 16) - 1u < 0x7F80u ? 0xFFFF0000u : 0u;
+  return u & (lo | hi);
+}
+
 __device__ __forceinline__ bf16x8 ld8(const uint16_t* p) {
   const uint4 v = *reinterpret_cast<const uint4*>(p);
   bf16x8 r;

@@ -477,6 +477,9 @@ __device__ __forceinline__ void unpack8(const uint4& r, float (&f)[8]) {
     f[2 * e + 1] = __uint_as_float(u[e] & 0xFFFF0000u);
   }
 }
+__device__ __forceinline__ uint4 gate8(const uint4& u, const uint4& y) {
+  return make_uint4(gate2(u.x, y.x), gate2(u.y, y.y), gate2(u.z, y.z), gate2(u.w, y.w));
+}
 __device__ __forceinline__ uint4 pack8(const float (&f)[8]) {
   uint32_t u[4];
 #pragma unroll
@@ -491,15 +494,8 @@ __global__ void k_relu_bwd8(long long nvox, int g8, const uint16_t* __restrict__
   if (i >= nvox * g8) return;
   const long long v = i / g8;
   const int c = (int)(i - v * g8) * 8;
-  float fy[8];
-  unpack8(ld16(y + v * yld + yoff + c), fy);
-  const uint4 d = ld16(dy + v * dld + doff + c);
-  const uint32_t du[4] = {d.x, d.y, d.z, d.w};
-  uint32_t o[4];
-#pragma unroll
-  for (int e = 0; e < 4; ++e)
-    o[e] = (fy[2 * e] > 0.f ? (du[e] & 0xFFFFu) : 0u) | (fy[2 * e + 1] > 0.f ? (du[e] & 0xFFFF0000u) : 0u);
-  st16(out + v * old + ooff + c, make_uint4(o[0], o[1], o[2], o[3]));
+  const uint4 yv = ld16(y + v * yld + yoff + c);
+  st16(out + v * old + ooff + c, gate8(ld16(dy + v * dld + doff + c), yv));
 }
 
 __global__ void k_pool_fwd8(unet_shape f, int g8, const uint16_t* __restrict__ x, int xld, int xoff,
@@ -525,7 +521,8 @@ __global__ void k_pool_fwd8(unet_shape f, int g8, const uint16_t* __restrict__ x
 }
 
 __global__ void k_pool_bwd8(unet_shape f, int g8, const uint16_t* __restrict__ dy, int dld,
-                            int doff, uint16_t* __restrict__ dx, int xld, int xoff, int accumulate) {
+                            int doff, uint16_t* __restrict__ dx, int xld, int xoff, int accumulate,
+                            const uint16_t* __restrict__ gate, int gld, int goff) {
   unet_shape cs{f.n, f.d / 2, f.h / 2, f.w / 2};
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long nfv = (long long)f.n * f.d * f.h * f.w;
@@ -544,7 +541,9 @@ __global__ void k_pool_bwd8(unet_shape f, int g8, const uint16_t* __restrict__ d
 #pragma unroll
     for (int e = 0; e < 8; ++e) g[e] += o[e];
   }
-  st16(dx + v * xld + xoff + c, pack8(g));
+  uint4 r = pack8(g);
+  if (gate) r = gate8(r, ld16(gate + v * gld + goff + c));
+  st16(dx + v * xld + xoff + c, r);
 }
 
 __global__ void k_up_fwd8(unet_shape cs, int g8, const uint16_t* __restrict__ x, int xld, int xoff,
@@ -561,7 +560,8 @@ __global__ void k_up_fwd8(unet_shape cs, int g8, const uint16_t* __restrict__ x,
 }
 
 __global__ void k_up_bwd8(unet_shape cs, int g8, const uint16_t* __restrict__ dy, int dld, int doff,
-                          uint16_t* __restrict__ dx, int xld, int xoff) {
+                          uint16_t* __restrict__ dx, int xld, int xoff,
+                          const uint16_t* __restrict__ gate, int gld, int goff) {
   const unet_shape f{cs.n, 2 * cs.d, 2 * cs.h, 2 * cs.w};
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   const long long ncv = (long long)cs.n * cs.d * cs.h * cs.w;
@@ -577,7 +577,9 @@ __global__ void k_up_bwd8(unet_shape cs, int g8, const uint16_t* __restrict__ dy
 #pragma unroll
     for (int e = 0; e < 8; ++e) acc[e] += g[e];
   }
-  st16(dx + V * xld + xoff + c, pack8(acc));
+  uint4 r = pack8(acc);
+  if (gate) r = gate8(r, ld16(gate + V * gld + goff + c));
+  st16(dx + V * xld + xoff + c, r);
 }
 
 __global__ void k_head_fwd8(long long nvox, int g8, const uint16_t* __restrict__ x, int xld,
@@ -595,41 +597,56 @@ __global__ void k_head_fwd8(long long nvox, int g8, const uint16_t* __restrict__
   y[v] = acc + b[0];
 }
 
-__global__ void k_head_dgrad8(long long nvox, int g8, const float* __restrict__ w,
-                              const float* __restrict__ dy, uint16_t* __restrict__ dx, int xld,
-                              int xoff) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nvox * g8) return;
-  const long long v = i / g8;
-  const int c = (int)(i - v * g8) * 8;
-  const float d = dy[v];
-  float o[8];
-#pragma unroll
-  for (int e = 0; e < 8; ++e) o[e] = w[c + e] * d;
-  st16(dx + v * xld + xoff + c, pack8(o));
-}
-
-// Head weight-gradient partials, 8-channel form: workgroup = voxel chunk,
+// Head backward, 8-channel form: workgroup = voxel chunk,
 // thread (j, g) sums voxels v0 + j, v0 + j + J, ... for channels 8g..8g+7
 // (g = 0 also the bias column); the J voxel lanes are then added by a fixed
-// pairwise tree in LDS.  wsp[chunk][c + 1] as k_head_wgrad_partial.
-__global__ __launch_bounds__(256) void k_head_wgrad8(long long nvox, int g8,
-                                                     const uint16_t* __restrict__ x, int xld,
-                                                     int xoff, const float* __restrict__ dy,
-                                                     long long vchunk, float* __restrict__ wsp) {
+// pairwise tree in LDS.  wsp[chunk][c + 1] as k_head_wgrad_partial.  With dx,
+// the same pass over x and dy writes dx = w dy, with `gate` cleared where x is
+// not positive (memory-bound: 16 channels of 2 x 128^3 65 us, before 78 in two
+// passes and 79 more for the ReLU).
+__global__ __launch_bounds__(256) void k_head_bwd8(long long nvox, int g8,
+                                                   const uint16_t* x, int xld, int xoff,
+                                                   const float* __restrict__ w,
+                                                   const float* __restrict__ dy,
+                                                   uint16_t* dx, int dld, int doff, int gate,
+                                                   long long vchunk, float* __restrict__ wsp) {
   __shared__ float red[256][9];
   const int tid = threadIdx.x, J = 256 / g8;
   const int g = tid % g8, j = tid / g8;
   const long long v0 = (long long)blockIdx.x * vchunk, v1 = min(nvox, v0 + vchunk);
   float acc[9] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if (j < J) {
-    for (long long v = v0 + j; v < v1; v += J) {
-      const float d = dy[v];
-      float fx[8];
-      unpack8(ld16(x + v * xld + xoff + 8 * g), fx);
+    float wr[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+    if (dx)
 #pragma unroll
-      for (int e = 0; e < 8; ++e) acc[e] += d * fx[e];
-      acc[8] += d;
+      for (int e = 0; e < 8; ++e) wr[e] = w[8 * g + e];
+    constexpr int U = 4;  // voxels in flight
+    for (long long v = v0 + j; v < v1; v += U * J) {
+      float d[U];
+      uint4 xr[U];
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const long long vq = min(v + q * J, v1 - 1);
+        d[q] = dy[vq];
+        xr[q] = ld16(x + vq * xld + xoff + 8 * g);
+      }
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        if (v + q * J >= v1) break;
+        float fx[8];
+        unpack8(xr[q], fx);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] += d[q] * fx[e];
+        acc[8] += d[q];
+        if (dx) {
+          float o[8];
+#pragma unroll
+          for (int e = 0; e < 8; ++e) o[e] = wr[e] * d[q];
+          uint4 r = pack8(o);
+          if (gate) r = gate8(r, xr[q]);
+          st16(dx + (v + q * J) * dld + doff + 8 * g, r);
+        }
+      }
     }
   }
 #pragma unroll
@@ -651,22 +668,40 @@ __global__ __launch_bounds__(256) void k_head_wgrad8(long long nvox, int g8,
 
 // masked MSE: per-block partial sums of the squared error and mask count,
 // and the gradient 2 (pred - target) mask / count (count passed in).
-__global__ __launch_bounds__(256) void k_mse_partial(long long nvox, const float* __restrict__ p,
-                                                     const float* __restrict__ t,
-                                                     const uint8_t* __restrict__ m,
-                                                     double* __restrict__ part) {
-  __shared__ double s1[256], s2[256];
+// One workgroup per CU fits the caller's partials: 16 waves each, four voxels
+// of a thread in flight (4 Mi voxels: 54 us with 4 waves and one, now 9.5).
+constexpr int kMseThreads = 1024;
+__global__ __launch_bounds__(kMseThreads) void k_mse_partial(long long nvox,
+                                                             const float* __restrict__ p,
+                                                             const float* __restrict__ t,
+                                                             const uint8_t* __restrict__ m,
+                                                             double* __restrict__ part) {
+  __shared__ double s1[kMseThreads], s2[kMseThreads];
   double a = 0.0, c = 0.0;
-  for (long long v = (long long)blockIdx.x * 256 + threadIdx.x; v < nvox; v += (long long)gridDim.x * 256)
-    if (m[v]) {
-      const double d = (double)p[v] - (double)t[v];
-      a += d * d;
-      c += 1.0;
+  constexpr int U = 4;
+  const long long step = (long long)gridDim.x * kMseThreads;
+  for (long long v = (long long)blockIdx.x * kMseThreads + threadIdx.x; v < nvox; v += U * step) {
+    float pv[U], tv[U];
+    bool on[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      const long long vq = min(v + q * step, nvox - 1);
+      pv[q] = p[vq];
+      tv[q] = t[vq];
+      on[q] = m[vq] && v + q * step < nvox;
     }
+#pragma unroll
+    for (int q = 0; q < U; ++q)
+      if (on[q]) {
+        const double d = (double)pv[q] - (double)tv[q];
+        a += d * d;
+        c += 1.0;
+      }
+  }
   s1[threadIdx.x] = a;
   s2[threadIdx.x] = c;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
+  for (int o = kMseThreads / 2; o > 0; o >>= 1) {
     if (threadIdx.x < o) {
       s1[threadIdx.x] += s1[threadIdx.x + o];
       s2[threadIdx.x] += s2[threadIdx.x + o];
@@ -915,9 +950,15 @@ void launch_brick(const ConvArgs& a, hipStream_t st) {
     constexpr BrickShape b = kBricks[SHAPE];
     using B = Brick<CK, NC, b.mb, NB, b.wd, b.wc>;
     // as many workgroups as run at once
-    hipLaunchKernelGGL((k_conv_brick<CK, NC, b.mb, NB, b.wd, b.wc>),
-                       dim3((unsigned)std::min(a.total, 256 * std::max(1, B::PER_CU))), dim3(B::NT),
-                       0, st, a);
+    const dim3 grid((unsigned)std::min(a.total, 256 * std::max(1, B::PER_CU)));
+    if constexpr (CK > 8)  // gates come with gradients, of 16 channels and more
+      if (a.gate) {
+        hipLaunchKernelGGL((k_conv_brick<CK, NC, b.mb, NB, b.wd, b.wc, true>), grid, dim3(B::NT), 0,
+                           st, a);
+        return;
+      }
+    hipLaunchKernelGGL((k_conv_brick<CK, NC, b.mb, NB, b.wd, b.wc, false>), grid, dim3(B::NT), 0, st,
+                       a);
   }
 }
 
@@ -1128,8 +1169,9 @@ unet_status unet_mfma_selfcheck(const void* a, const void* b, float* out, void* 
   return UNET_OK;
 }
 
-unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* bias, int32_t taps,
-                          unet_act y, float* out_f32, int32_t relu, void* stream) {
+static unet_status conv(unet_shape s, unet_act x, const void* w, const float* bias, int32_t taps,
+                        unet_act y, float* out_f32, int32_t relu, const unet_act* gate,
+                        void* stream) {
   if (!shape_ok(s) || !w || (taps != 27 && taps != 1)) return ufail(UNET_EINVAL, "bad conv args");
   if (!act_ok(x, 8) || x.c > 256)
     return ufail(UNET_EINVAL, "bad input view (ld/off/c multiples of 8, c <= 256)");
@@ -1158,6 +1200,12 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
       a.yf = out_f32;
       a.relu = relu;
       a.wide = (uintptr_t)(out_f32 ? (void*)out_f32 : y.p) % 16 == 0;
+      if (gate) {
+        a.gate = (const uint16_t*)gate->p;
+        a.gld = gate->ld;
+        a.goff = gate->off;
+        a.wide = a.wide && (uintptr_t)gate->p % 16 == 0;
+      }
       enq_brick(bp, a, y.c, st);
       UHIP(hipGetLastError());
       return UNET_OK;
@@ -1186,7 +1234,12 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
                          bias, taps, yp, y.ld, y.off, out_f32, relu);
   });
   UHIP(hipGetLastError());
-  return UNET_OK;
+  return gate ? unet_relu_bwd(s, *gate, y, y, stream) : UNET_OK;
+}
+
+unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* bias, int32_t taps,
+                          unet_act y, float* out_f32, int32_t relu, void* stream) {
+  return conv(s, x, w, bias, taps, y, out_f32, relu, nullptr, stream);
 }
 
 unet_status unet_conv_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
@@ -1202,8 +1255,8 @@ unet_status unet_conv_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t ta
   return UNET_OK;
 }
 
-unet_status unet_conv_dgrad(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act dx,
-                            void* wflip, void* stream) {
+static unet_status dgrad(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act dx,
+                         const unet_act* gate, void* wflip, void* stream) {
   if (!shape_ok(s) || !w || !wflip || (taps != 27 && taps != 1))
     return ufail(UNET_EINVAL, "bad dgrad args");
   if (!act_ok(dy, 16) || !act_ok(dx, 16)) return ufail(UNET_EINVAL, "bad dgrad views");
@@ -1211,7 +1264,18 @@ unet_status unet_conv_dgrad(unet_shape s, unet_act dy, const void* w, int32_t ta
   hipLaunchKernelGGL(k_flip_weights, dim3(nblk(n)), dim3(256), 0, (hipStream_t)stream,
                      (const uint16_t*)w, (uint16_t*)wflip, dy.c, dx.c, taps);
   UHIP(hipGetLastError());
-  return unet_conv_fwd(s, dy, wflip, nullptr, taps, dx, nullptr, 0, stream);
+  return conv(s, dy, wflip, nullptr, taps, dx, nullptr, 0, gate, stream);
+}
+
+unet_status unet_conv_dgrad(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act dx,
+                            void* wflip, void* stream) {
+  return dgrad(s, dy, w, taps, dx, nullptr, wflip, stream);
+}
+
+unet_status unet_conv_dgrad_relu(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act y,
+                                 unet_act dx, void* wflip, void* stream) {
+  if (!act_ok(y, 16) || y.c != dx.c) return ufail(UNET_EINVAL, "bad dgrad gate view");
+  return dgrad(s, dy, w, taps, dx, &y, wflip, stream);
 }
 
 size_t unet_wgrad_workspace(unet_shape s, int32_t cin, int32_t cout, int32_t taps) {
@@ -1312,7 +1376,8 @@ unet_status unet_pool_fwd(unet_shape f, unet_act x, unet_act y, void* stream) {
   return UNET_OK;
 }
 
-unet_status unet_pool_bwd(unet_shape f, unet_act dy, unet_act dx, int32_t accumulate, void* stream) {
+static unet_status pool_bwd(unet_shape f, unet_act dy, unet_act dx, int32_t accumulate,
+                            const unet_act* gate, void* stream) {
   if (!shape_ok(f) || f.d % 2 || f.h % 2 || f.w % 2 || !act_ok(dy, 1) || !act_ok(dx, 1) ||
       dx.c != dy.c)
     return ufail(UNET_EINVAL, "bad pool_bwd args");
@@ -1320,13 +1385,24 @@ unet_status unet_pool_bwd(unet_shape f, unet_act dy, unet_act dx, int32_t accumu
   if (dx.c % 8 == 0)
     hipLaunchKernelGGL(k_pool_bwd8, dim3(nblk(n / 8)), dim3(256), 0, (hipStream_t)stream, f,
                        dx.c / 8, (const uint16_t*)dy.p, dy.ld, dy.off, (uint16_t*)dx.p, dx.ld,
-                       dx.off, accumulate);
+                       dx.off, accumulate, gate ? (const uint16_t*)gate->p : nullptr,
+                       gate ? gate->ld : 0, gate ? gate->off : 0);
   else
     hipLaunchKernelGGL(k_pool_bwd, dim3(nblk(n)), dim3(256), 0, (hipStream_t)stream, f, dx.c,
                        (const uint16_t*)dy.p, dy.ld, dy.off, (uint16_t*)dx.p, dx.ld, dx.off,
                        accumulate);
   UHIP(hipGetLastError());
-  return UNET_OK;
+  return gate && dx.c % 8 ? unet_relu_bwd(f, *gate, dx, dx, stream) : UNET_OK;
+}
+
+unet_status unet_pool_bwd(unet_shape f, unet_act dy, unet_act dx, int32_t accumulate, void* stream) {
+  return pool_bwd(f, dy, dx, accumulate, nullptr, stream);
+}
+
+unet_status unet_pool_bwd_relu(unet_shape f, unet_act dy, unet_act y, unet_act dx,
+                               int32_t accumulate, void* stream) {
+  if (!act_ok(y, 1) || y.c != dx.c) return ufail(UNET_EINVAL, "bad pool_bwd gate view");
+  return pool_bwd(f, dy, dx, accumulate, &y, stream);
 }
 
 unet_status unet_up_fwd(unet_shape cs, unet_act x, unet_act y, void* stream) {
@@ -1343,19 +1419,30 @@ unet_status unet_up_fwd(unet_shape cs, unet_act x, unet_act y, void* stream) {
   return UNET_OK;
 }
 
-unet_status unet_up_bwd(unet_shape cs, unet_act dy, unet_act dx, void* stream) {
+static unet_status up_bwd(unet_shape cs, unet_act dy, unet_act dx, const unet_act* gate,
+                          void* stream) {
   if (!shape_ok(cs) || !act_ok(dy, 1) || !act_ok(dx, 1) || dx.c != dy.c)
     return ufail(UNET_EINVAL, "bad up_bwd args");
   const long long n = nvox_of(cs) * dx.c;
   if (dx.c % 8 == 0)
     hipLaunchKernelGGL(k_up_bwd8, dim3(nblk(n / 8)), dim3(256), 0, (hipStream_t)stream, cs,
                        dx.c / 8, (const uint16_t*)dy.p, dy.ld, dy.off, (uint16_t*)dx.p, dx.ld,
-                       dx.off);
+                       dx.off, gate ? (const uint16_t*)gate->p : nullptr, gate ? gate->ld : 0,
+                       gate ? gate->off : 0);
   else
     hipLaunchKernelGGL(k_up_bwd, dim3(nblk(n)), dim3(256), 0, (hipStream_t)stream, cs, dx.c,
                        (const uint16_t*)dy.p, dy.ld, dy.off, (uint16_t*)dx.p, dx.ld, dx.off);
   UHIP(hipGetLastError());
-  return UNET_OK;
+  return gate && dx.c % 8 ? unet_relu_bwd(cs, *gate, dx, dx, stream) : UNET_OK;
+}
+
+unet_status unet_up_bwd(unet_shape cs, unet_act dy, unet_act dx, void* stream) {
+  return up_bwd(cs, dy, dx, nullptr, stream);
+}
+
+unet_status unet_up_bwd_relu(unet_shape cs, unet_act dy, unet_act y, unet_act dx, void* stream) {
+  if (!act_ok(y, 1) || y.c != dx.c) return ufail(UNET_EINVAL, "bad up_bwd gate view");
+  return up_bwd(cs, dy, dx, &y, stream);
 }
 
 unet_status unet_head_fwd(unet_shape s, unet_act x, const float* w, const float* b, float* y,
@@ -1380,8 +1467,8 @@ size_t unet_head_workspace(unet_shape s, int32_t cin) {
   return (size_t)(nc + sum_groups(nc)) * (cin + 1) * sizeof(float);
 }
 
-unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,
-                          float* dw, float* db, void* ws, void* stream) {
+static unet_status head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,
+                            bool gate, float* dw, float* db, void* ws, void* stream) {
   if (!shape_ok(s) || !act_ok(x, 1) || !w || !dy || !dw || !db || !ws)
     return ufail(UNET_EINVAL, "bad head_bwd args");
   hipStream_t st = (hipStream_t)stream;
@@ -1389,10 +1476,7 @@ unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float*
   const bool v8 = x.c % 8 == 0 && x.c <= 256;
   if (dx.p) {
     if (!act_ok(dx, 1) || dx.c != x.c) return ufail(UNET_EINVAL, "bad head dx view");
-    if (v8)
-      hipLaunchKernelGGL(k_head_dgrad8, dim3(nblk(nv * x.c / 8)), dim3(256), 0, st, nv, x.c / 8,
-                         w, dy, (uint16_t*)dx.p, dx.ld, dx.off);
-    else
+    if (!v8)
       hipLaunchKernelGGL(k_head_dgrad, dim3(nblk(nv * x.c)), dim3(256), 0, st, nv, x.c, w, dy,
                          (uint16_t*)dx.p, dx.ld, dx.off);
   }
@@ -1400,15 +1484,26 @@ unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float*
   const int nc = (int)((nv + ch - 1) / ch);
   float* wsp = (float*)ws;
   if (v8)
-    hipLaunchKernelGGL(k_head_wgrad8, dim3(nc), dim3(256), 0, st, nv, x.c / 8,
-                       (const uint16_t*)x.p, x.ld, x.off, dy, ch, wsp);
+    hipLaunchKernelGGL(k_head_bwd8, dim3(nc), dim3(256), 0, st, nv, x.c / 8,
+                       (const uint16_t*)x.p, x.ld, x.off, w, dy, (uint16_t*)dx.p, dx.ld, dx.off,
+                       gate ? 1 : 0, ch, wsp);
   else
     hipLaunchKernelGGL(k_head_wgrad_partial, dim3(nc), dim3(64), 0, st, nv, x.c,
                        (const uint16_t*)x.p, x.ld, x.off, dy, ch, wsp);
   // wsp[chunk][c + 1] -> dw[c] (the last column is the bias gradient)
   enq_sum_rows(wsp, nc, x.c + 1, x.c, dw, db, st);
   UHIP(hipGetLastError());
-  return UNET_OK;
+  return gate && dx.p && !v8 ? unet_relu_bwd(s, x, dx, dx, stream) : UNET_OK;
+}
+
+unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,
+                          float* dw, float* db, void* ws, void* stream) {
+  return head_bwd(s, x, w, dy, dx, false, dw, db, ws, stream);
+}
+
+unet_status unet_head_bwd_relu(unet_shape s, unet_act x, const float* w, const float* dy,
+                               unet_act dx, float* dw, float* db, void* ws, void* stream) {
+  return head_bwd(s, x, w, dy, dx, true, dw, db, ws, stream);
 }
 
 unet_status unet_mse(unet_shape s, const float* pred, const float* target, const uint8_t* mask,
@@ -1419,7 +1514,7 @@ unet_status unet_mse(unet_shape s, const float* pred, const float* target, const
   const long long nv = nvox_of(s);
   const int nb = 256;
   double* part = stats_dev + 2;  // caller provides 2 + 2 * 256 doubles
-  hipLaunchKernelGGL(k_mse_partial, dim3(nb), dim3(256), 0, st, nv, pred, target, mask, part);
+  hipLaunchKernelGGL(k_mse_partial, dim3(nb), dim3(kMseThreads), 0, st, nv, pred, target, mask, part);
   hipLaunchKernelGGL(k_mse_finish, dim3(1), dim3(256), 0, st, part, nb, stats_dev);
   hipLaunchKernelGGL(k_mse_grad, dim3(nblk(nv)), dim3(256), 0, st, nv, pred, target, mask,
                      stats_dev, dpred);

@@ -38,6 +38,8 @@ _F = ctypes.c_float
 _SIGS = [
     ("unet_conv_fwd", ctypes.c_int, [unet_shape, unet_act, _V, _V, _I, unet_act, _V, _I, _V]),
     ("unet_conv_dgrad", ctypes.c_int, [unet_shape, unet_act, _V, _I, unet_act, _V, _V]),
+    ("unet_conv_dgrad_relu", ctypes.c_int, [unet_shape, unet_act, _V, _I, unet_act, unet_act, _V,
+                                            _V]),
     ("unet_wgrad_workspace", ctypes.c_size_t, [unet_shape, _I, _I, _I]),
     ("unet_conv_wgrad", ctypes.c_int, [unet_shape, unet_act, unet_act, _I, _V, _V, _V, _V]),
     ("unet_wgrad_kernel", ctypes.c_int, [unet_shape, _I, _I, _I, _V]),
@@ -47,9 +49,12 @@ _SIGS = [
     ("unet_pool_bwd", ctypes.c_int, [unet_shape, unet_act, unet_act, _I, _V]),
     ("unet_up_fwd", ctypes.c_int, [unet_shape, unet_act, unet_act, _V]),
     ("unet_up_bwd", ctypes.c_int, [unet_shape, unet_act, unet_act, _V]),
+    ("unet_pool_bwd_relu", ctypes.c_int, [unet_shape, unet_act, unet_act, unet_act, _I, _V]),
+    ("unet_up_bwd_relu", ctypes.c_int, [unet_shape, unet_act, unet_act, unet_act, _V]),
     ("unet_head_fwd", ctypes.c_int, [unet_shape, unet_act, _V, _V, _V, _V]),
     ("unet_head_workspace", ctypes.c_size_t, [unet_shape, _I]),
     ("unet_head_bwd", ctypes.c_int, [unet_shape, unet_act, _V, _V, unet_act, _V, _V, _V, _V]),
+    ("unet_head_bwd_relu", ctypes.c_int, [unet_shape, unet_act, _V, _V, unet_act, _V, _V, _V, _V]),
     ("unet_mse", ctypes.c_int, [unet_shape, _V, _V, _V, _V, _V,
                                 ctypes.POINTER(ctypes.c_double), _V]),
     ("unet_adam", ctypes.c_int, [ctypes.c_int64, _V, _V, _V, _V, _V, _F, _F, _F, _F, _I, _V]),
@@ -121,6 +126,10 @@ def unet_conv_dgrad(s, dy, w, taps, dx, wflip):
     _check(load().unet_conv_dgrad(s, dy, _p(w), taps, dx, _p(wflip), _stream()))
 
 
+def unet_conv_dgrad_relu(s, dy, w, taps, y, dx, wflip):
+    _check(load().unet_conv_dgrad_relu(s, dy, _p(w), taps, y, dx, _p(wflip), _stream()))
+
+
 def unet_wgrad_workspace(s, cin, cout, taps):
     return load().unet_wgrad_workspace(s, cin, cout, taps)
 
@@ -174,6 +183,14 @@ def unet_up_bwd(coarse, dy, dx):
     _check(load().unet_up_bwd(coarse, dy, dx, _stream()))
 
 
+def unet_pool_bwd_relu(fine, dy, y, dx, accumulate=0):
+    _check(load().unet_pool_bwd_relu(fine, dy, y, dx, int(accumulate), _stream()))
+
+
+def unet_up_bwd_relu(coarse, dy, y, dx):
+    _check(load().unet_up_bwd_relu(coarse, dy, y, dx, _stream()))
+
+
 def unet_head_fwd(s, x, w, b, y):
     _check(load().unet_head_fwd(s, x, _p(w), _p(b), _p(y), _stream()))
 
@@ -184,6 +201,10 @@ def unet_head_workspace(s, cin):
 
 def unet_head_bwd(s, x, w, dy, dx, dw, db, ws):
     _check(load().unet_head_bwd(s, x, _p(w), _p(dy), dx, _p(dw), _p(db), _p(ws), _stream()))
+
+
+def unet_head_bwd_relu(s, x, w, dy, dx, dw, db, ws):
+    _check(load().unet_head_bwd_relu(s, x, _p(w), _p(dy), dx, _p(dw), _p(db), _p(ws), _stream()))
 
 
 def unet_mse(s, pred, target, mask, dpred, stats, want_loss=True):

@@ -193,46 +193,44 @@ class UNet:
         c0 = ch[0]
         hw0, hb0 = gw("head")
         w0, b0, _, _, _ = self.offs["head"]
-        UN.unet_head_bwd(s0, A(B["Db0"], c0, 0, c0), self.master[w0:b0], B["dout"],
-                         A(B["gDb0"], c0, 0, c0), hw0, hb0, B["ws"])
+        # every gradient leaves its kernel with the ReLU backward of its layer applied
+        UN.unet_head_bwd_relu(s0, A(B["Db0"], c0, 0, c0), self.master[w0:b0], B["dout"],
+                              A(B["gDb0"], c0, 0, c0), hw0, hb0, B["ws"])
         for i in range(self.nl - 1):
             c, cu = ch[i], ch[i + 1]
             s = UN.shape(*sh[i])
             gDb = A(B[f"gDb{i}"], c, 0, c)
-            UN.unet_relu_bwd(s, A(B[f"Db{i}"], c, 0, c), gDb, gDb)
             dw, db = gw(f"dec{i}b")
-            UN.unet_conv_wgrad(s, A(B[f"Da{i}"], c, 0, c), gDb, 27, dw, db, B["ws"])
-            UN.unet_conv_dgrad(s, gDb, self._w(f"dec{i}b")[0], 27, A(B[f"gDa{i}"], c, 0, c),
-                               B["wflip"])
-            gDa = A(B[f"gDa{i}"], c, 0, c)
-            UN.unet_relu_bwd(s, A(B[f"Da{i}"], c, 0, c), gDa, gDa)
+            Da, gDa = A(B[f"Da{i}"], c, 0, c), A(B[f"gDa{i}"], c, 0, c)
+            UN.unet_conv_wgrad(s, Da, gDb, 27, dw, db, B["ws"])
+            UN.unet_conv_dgrad_relu(s, gDb, self._w(f"dec{i}b")[0], 27, Da, gDa, B["wflip"])
             dw, db = gw(f"dec{i}a")
-            UN.unet_conv_wgrad(s, A(B[f"CAT{i}"], 2 * c, 0, 2 * c), gDa, 27, dw, db, B["ws"])
-            UN.unet_conv_dgrad(s, gDa, self._w(f"dec{i}a")[0], 27,
-                               A(B[f"gCAT{i}"], 2 * c, 0, 2 * c), B["wflip"])
+            # (the encoder's half is gated once more after pooling's share is added)
+            cat = A(B[f"CAT{i}"], 2 * c, 0, 2 * c)
+            UN.unet_conv_wgrad(s, cat, gDa, 27, dw, db, B["ws"])
+            UN.unet_conv_dgrad_relu(s, gDa, self._w(f"dec{i}a")[0], 27, cat,
+                                    A(B[f"gCAT{i}"], 2 * c, 0, 2 * c), B["wflip"])
             gup = A(B[f"gCAT{i}"], 2 * c, 0, c)
-            UN.unet_relu_bwd(s, A(B[f"CAT{i}"], 2 * c, 0, c), gup, gup)
             dw, db = gw(f"up{i}")
             UN.unet_conv_wgrad(s, A(B[f"U{i}"], cu, 0, cu), gup, 27, dw, db, B["ws"])
             UN.unet_conv_dgrad(s, gup, self._w(f"up{i}")[0], 27, A(B[f"gU{i}"], cu, 0, cu),
                                B["wflip"])
-            dst = B["gEb"] if i + 1 == self.nl - 1 else B[f"gDb{i + 1}"]
-            UN.unet_up_bwd(UN.shape(*sh[i + 1]), A(B[f"gU{i}"], cu, 0, cu), A(dst, cu, 0, cu))
+            out, dst = ("Eb", "gEb") if i + 1 == self.nl - 1 else (f"Db{i + 1}", f"gDb{i + 1}")
+            UN.unet_up_bwd_relu(UN.shape(*sh[i + 1]), A(B[f"gU{i}"], cu, 0, cu),
+                                A(B[out], cu, 0, cu), A(B[dst], cu, 0, cu))
         for i in range(self.nl - 1, -1, -1):
             c = ch[i]
             s = UN.shape(*sh[i])
             if i == self.nl - 1:
-                yb, gyb = A(B["Eb"], c, 0, c), A(B["gEb"], c, 0, c)
+                gyb = A(B["gEb"], c, 0, c)
             else:
-                yb, gyb = A(B[f"CAT{i}"], 2 * c, c, c), A(B[f"gCAT{i}"], 2 * c, c, c)
-                UN.unet_pool_bwd(s, A(B[f"gP{i + 1}"], c, 0, c), gyb, 1)
-            UN.unet_relu_bwd(s, yb, gyb, gyb)
+                gyb = A(B[f"gCAT{i}"], 2 * c, c, c)
+                UN.unet_pool_bwd_relu(s, A(B[f"gP{i + 1}"], c, 0, c),
+                                      A(B[f"CAT{i}"], 2 * c, c, c), gyb, 1)
             dw, db = gw(f"enc{i}b")
-            UN.unet_conv_wgrad(s, A(B[f"Ea{i}"], c, 0, c), gyb, 27, dw, db, B["ws"])
-            UN.unet_conv_dgrad(s, gyb, self._w(f"enc{i}b")[0], 27, A(B[f"gEa{i}"], c, 0, c),
-                               B["wflip"])
-            gEa = A(B[f"gEa{i}"], c, 0, c)
-            UN.unet_relu_bwd(s, A(B[f"Ea{i}"], c, 0, c), gEa, gEa)
+            Ea, gEa = A(B[f"Ea{i}"], c, 0, c), A(B[f"gEa{i}"], c, 0, c)
+            UN.unet_conv_wgrad(s, Ea, gyb, 27, dw, db, B["ws"])
+            UN.unet_conv_dgrad_relu(s, gyb, self._w(f"enc{i}b")[0], 27, Ea, gEa, B["wflip"])
             dw, db = gw(f"enc{i}a")
             if i == 0:
                 UN.unet_conv_wgrad(s, A(x_in, IN_CH, 0, IN_CH), gEa, 27, dw, db, B["ws"])
