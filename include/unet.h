@@ -66,8 +66,8 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
  * multiple of 8), 0 for everything else; info[1] = tile width (class 1) or
  * voxel blocks of 16 per wave (class 0); info[2] = output blocks of 16 per
  * wave; info[3] = output-channel groups (workgroups that share an input
- * tile).  3x3x3 convolutions of both classes run the brick kernel, which
- * chooses its own bricks; the blocking is that of the gathered kernel (1x1x1
+ * tile).  3x3x3 convolutions of both classes run the brick or marching kernels,
+ * which choose their own tiles; the blocking is that of the gathered kernel (1x1x1
  * taps, or h * w * ld of 2^27 and more).  info: 4 int32 written by the call.
  * UNET_EINVAL for a bad shape, channel count (cin a multiple of 8 up to 256;
  * cout 16, 32, 64 or 128) or taps. */

@@ -999,6 +999,47 @@ void enq_brick(const BrickPlan& p, ConvArgs a, int cout, hipStream_t st) {
   }
 }
 
+// Enqueues the marching kernel if it takes these sizes and is the faster one:
+// from 9 planes per CU on, its two steps of start and its larger tiles pay off.
+// Marching against bricks, us (planes per CU): 8 -> 16 on 2 x 128^3 (32) 49 / 61,
+// on 48x56x104 (3) 11.1 / 10.7; 16 -> 16 on 2 x 128^3 72 / 91, 100x90x120 (9) 27.7 /
+// 28.7, 48x56x104 15.5 / 11.5; 16 -> 32 on 2 x 128^3 135 / 166, 2 x 64^3 (8) 22.8 /
+// 22.7; 32 -> 16 on 2 x 128^3 131 / 158, 100x90x120 42.8 / 43.7, 64^3 (2) 15.4 / 11.9;
+// 32 -> 32 on 2 x 64^3 (8) 37.5 / 36.4, 32 -> 64 (16) 64.5 / 68.3.
+template <typename K>
+bool enq_march(ConvArgs a, int cout, hipStream_t st, K) {
+  if (cout / 16 % K::NB) return false;
+  a.nbw = (a.s.w + 16 * K::WW - 1) / (16 * K::WW);
+  a.nbh = (a.s.h + K::MB * K::WH - 1) / (K::MB * K::WH);
+  const long long steps = (long long)a.s.n * a.nbw * a.nbh * a.s.d;
+  const int groups = cout / 16 / K::NB;
+  const long long nchunk = std::min(steps, std::max(1LL, 256LL * K::PER_CU / groups));
+  if (steps * groups < 9 * 256) return false;
+  a.q = (int)(steps / nchunk);
+  a.r = (int)(steps % nchunk);
+  const dim3 grid((unsigned)nchunk, (unsigned)groups);
+  if constexpr (K::CK > 8)
+    if (a.gate) {
+      hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, true>), grid,
+                         dim3(K::NT), 0, st, a);
+      return true;
+    }
+  hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, false>), grid,
+                     dim3(K::NT), 0, st, a);
+  return true;
+}
+
+bool march(const ConvArgs& a, int cout, hipStream_t st) {
+  // offsets within a plane are 32-bit
+  if ((long long)a.s.h * a.s.w * a.xld >= (1LL << 30) - 64) return false;
+  if (a.cin == 8) return enq_march(a, cout, st, unet::March<8, 1, 8, 2, 2>{});
+  if (a.cin == 16)
+    return cout % 32 ? enq_march(a, cout, st, unet::March<16, 1, 8, 2, 2>{})
+                     : enq_march(a, cout, st, unet::March<16, 2, 4, 2, 2>{});
+  if (a.cin == 32) return enq_march(a, cout, st, unet::March<32, 1, 4, 2, 4>{});
+  return false;
+}
+
 // Rows of workspace past the chunks' (part of the size callers allocate).
 long long sum_groups(long long nchunk) { return nchunk > 64 ? (nchunk + 63) / 64 : 0; }
 
@@ -1206,7 +1247,7 @@ static unet_status conv(unet_shape s, unet_act x, const void* w, const float* bi
         a.goff = gate->off;
         a.wide = a.wide && (uintptr_t)gate->p % 16 == 0;
       }
-      enq_brick(bp, a, y.c, st);
+      if (!march(a, y.c, st)) enq_brick(bp, a, y.c, st);
       UHIP(hipGetLastError());
       return UNET_OK;
     }
