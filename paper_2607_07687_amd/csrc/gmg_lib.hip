@@ -85,31 +85,34 @@ __device__ __forceinline__ void walk_column_s(const Geom& g, const T* __restrict
 // r = sigma - A x on active cells (0 elsewhere) for column (i, j) over the
 // z-planes [k0, k1); optional store of r; returns the column's sum of r^2.
 // Faces through face(d, q, hi) (walk_column_vsf, PF planes of loads in
-// flight).
-template <typename T, int PF = 2, typename FL>
+// flight).  SN: *s2 gets the sum of sigma^2 over the active cells (D != 0).
+template <typename T, int PF = 2, bool SN = false, typename FL>
 __device__ __forceinline__ double residual_column_f(const Geom& g, const T* __restrict__ x,
                                                     const T* __restrict__ sigma, FL&& face,
                                                     T* __restrict__ r, int i, int j, int k0,
-                                                    int k1) {
-  double acc = 0.0;
+                                                    int k1, double* s2 = nullptr) {
+  double acc = 0.0, as = 0.0;
   walk_column_vsf<T, PF>(
       g, [&](long long q) { return x[q]; }, [&](long long q) { return sigma[q]; }, face, i, j,
       k0, k1, [&](long long idx, T ax, T D, T, T sv) {
         const T rv = (D != T(0)) ? sv - ax : T(0);
         if (r) r[idx] = rv;
         acc += (double)rv * (double)rv;
+        if (SN && D != T(0)) as += (double)sv * (double)sv;
       });
+  if (SN) *s2 = as;
   return acc;
 }
 
-template <typename T, typename TL>
+template <typename T, typename TL, bool SN = false>
 __device__ __forceinline__ double residual_column(const Geom& g, const T* __restrict__ x,
                                                   const T* __restrict__ sigma,
                                                   const TL* __restrict__ L, T* __restrict__ r,
-                                                  int i, int j, int k0, int k1) {
-  return residual_column_f<T>(
+                                                  int i, int j, int k0, int k1,
+                                                  double* s2 = nullptr) {
+  return residual_column_f<T, 2, SN>(
       g, x, sigma, [&](int d, long long q, bool) { return ldL<T>(L + d * g.n, q); }, r, i, j, k0,
-      k1);
+      k1, s2);
 }
 
 __device__ __forceinline__ bool same_bits(double a, double b) {
@@ -244,28 +247,39 @@ template <typename T>
 constexpr int kResPF = sizeof(T) == 4 ? 3 : 2;
 
 // r = sigma - A x over a chunk of z-planes; one FP64 partial of r^2 per block
-// (stored by the block's z-chunk, whatever the dispatch order).
-template <typename T, typename TL>
+// (stored by the block's z-chunk, whatever the dispatch order).  SN: and one of
+// sigma^2 over the active cells into spart, in the order of k_masked_sumsq
+// (active <=> D != 0, as in the mask): bitwise its partials without its pass over
+// sigma and the mask (512 x 192 x 192 with r and both norms: 135 -> 90.5 us a call).
+template <typename T, typename TL, bool SN = false>
 __global__ __launch_bounds__(BT) void k_residual(Geom g, Roles<T> X, int role,
                                                  const T* __restrict__ sigma,
                                                  const TL* __restrict__ L, T* r,
                                                  double* partials, int kchunk, const int* done,
-                                                 int zper, const UBrick* ub, int ubx, int uby) {
+                                                 int zper, const UBrick* ub, int ubx, int uby,
+                                                 double* spart = nullptr) {
   if (stopped(done)) return;
   const int3 b = xcd_block();
   const int zb = chunk_top_first(b.z, gridDim.z, zper);
   const int k0 = zb * kchunk, k1 = min(g.nz, k0 + kchunk);
   const int i = b.x * BX + threadIdx.x, j = b.y * BY + threadIdx.y;
-  double u[3];
+  double u[3], s2 = 0.0;
   const double acc =
       uniform_block(ub, ubx, uby, b.x, b.y, k0, k1, u)
-          ? residual_column_f<T, kResPF<T>>(g, X.get(role), sigma, UniformFaces<T>(g, u, i, j, k0),
-                                            r, i, j, k0, k1)
-          : residual_column<T, TL>(g, X.get(role), sigma, L, r, i, j, k0, k1);
+          ? residual_column_f<T, kResPF<T>, SN>(g, X.get(role), sigma,
+                                                UniformFaces<T>(g, u, i, j, k0), r, i, j, k0, k1,
+                                                &s2)
+          : residual_column<T, TL, SN>(g, X.get(role), sigma, L, r, i, j, k0, k1, &s2);
+  const int tid = threadIdx.x + BX * threadIdx.y;
+  const long long blk = ((long long)zb * gridDim.y + b.y) * gridDim.x + b.x;
   if (partials) {
-    const int tid = threadIdx.x + BX * threadIdx.y;
     const double s = block_sum(acc, tid, BT);
-    if (tid == 0) partials[((long long)zb * gridDim.y + b.y) * gridDim.x + b.x] = s;
+    if (tid == 0) partials[blk] = s;
+  }
+  if constexpr (SN) {
+    __syncthreads();
+    const double s = block_sum(s2, tid, BT);
+    if (tid == 0) spart[blk] = s;
   }
 }
 
@@ -681,9 +695,11 @@ __global__ __launch_bounds__(256) void k_spec_finish(const double* p, long long 
 
 __global__ void k_set_omega(SolveState* st, double omega) { st->omega = omega; }
 
-__global__ __launch_bounds__(256) void k_sum_to(const double* p, long long n, double* out) {
-  const double s = reduce_partials(p, n);
-  if (threadIdx.x == 0) *out = s;
+// (block b: the set of partials b * stride further on, into out[b])
+__global__ __launch_bounds__(256) void k_sum_to(const double* p, long long n, double* out,
+                                                long long stride) {
+  const double s = reduce_partials(p + blockIdx.x * stride, n);
+  if (threadIdx.x == 0) out[blockIdx.x] = s;
 }
 
 // Number of active cells (per-block partials, z-chunked).
@@ -2256,23 +2272,26 @@ gmg_status gmg_residual(gmg_handle* h, const void* x, const void* sigma, void* r
   } else {
     DISPATCH_CYCLE(h, {
       Roles<T> X{{(T*)x, (T*)x, (T*)x}, nullptr};
-      hipLaunchKernelGGL((k_residual<T, TL>), gr, kBlock, 0, h->s, lv.g, X, 0, (const T*)sigma,
-                         (const TL*)lv.L, (T*)r, pa, kResChunk, nullptr, 1, lv.ub, lv.ubx,
-                         lv.uby);
       if (snorm)
-        hipLaunchKernelGGL((k_masked_sumsq<T>), gr, kBlock, 0, h->s, lv.g, (const T*)sigma,
-                           lv.active, h->partials + h->maxpart, kResChunk);
+        hipLaunchKernelGGL((k_residual<T, TL, true>), gr, kBlock, 0, h->s, lv.g, X, 0,
+                           (const T*)sigma, (const TL*)lv.L, (T*)r, pa, kResChunk, nullptr, 1,
+                           lv.ub, lv.ubx, lv.uby, h->partials + h->maxpart);
+      else
+        hipLaunchKernelGGL((k_residual<T, TL>), gr, kBlock, 0, h->s, lv.g, X, 0, (const T*)sigma,
+                           (const TL*)lv.L, (T*)r, pa, kResChunk, nullptr, 1, lv.ub, lv.ubx,
+                           lv.uby, nullptr);
     });
   }
   HIP_TRY(hipGetLastError());
   if (!rnorm && !snorm) return GMG_OK;
   // reduce both partial sets into the state's scratch, then read them back
-  if (rnorm)
-    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(256), 0, h->s, h->partials, nblocks(gr),
-                       &h->st->scr[0]);
-  if (snorm)
-    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(256), 0, h->s, h->partials + h->maxpart,
-                       nblocks(gr), &h->st->scr[1]);
+  if (rnorm && snorm)
+    hipLaunchKernelGGL(k_sum_to, dim3(2), dim3(256), 0, h->s, h->partials, nblocks(gr),
+                       &h->st->scr[0], h->maxpart);
+  else
+    hipLaunchKernelGGL(k_sum_to, dim3(1), dim3(256), 0, h->s,
+                       h->partials + (snorm ? h->maxpart : 0), nblocks(gr),
+                       &h->st->scr[snorm ? 1 : 0], 0LL);
   HIP_TRY(hipGetLastError());
   double tmp[2] = {0.0, 0.0};
   HIP_TRY(hipMemcpyAsync(tmp, &h->st->scr[0], 2 * sizeof(double), hipMemcpyDeviceToHost, h->s));
@@ -2306,12 +2325,14 @@ gmg_status gmg_residual_noalloc(gmg_handle* h, const void* x, const void* sigma,
   } else {
     DISPATCH_CYCLE(h, {
       Roles<T> X{{(T*)x, (T*)x, (T*)x}, nullptr};
-      hipLaunchKernelGGL((k_residual<T, TL>), gr, kBlock, 0, h->s, lv.g, X, 0, (const T*)sigma,
-                         (const TL*)lv.L, (T*)r, pr, kResChunk, nullptr, 1, lv.ub, lv.ubx,
-                         lv.uby);
       if (snorm)
-        hipLaunchKernelGGL((k_masked_sumsq<T>), gr, kBlock, 0, h->s, lv.g, (const T*)sigma,
-                           lv.active, ps, kResChunk);
+        hipLaunchKernelGGL((k_residual<T, TL, true>), gr, kBlock, 0, h->s, lv.g, X, 0,
+                           (const T*)sigma, (const TL*)lv.L, (T*)r, pr, kResChunk, nullptr, 1,
+                           lv.ub, lv.ubx, lv.uby, ps);
+      else
+        hipLaunchKernelGGL((k_residual<T, TL>), gr, kBlock, 0, h->s, lv.g, X, 0, (const T*)sigma,
+                           (const TL*)lv.L, (T*)r, pr, kResChunk, nullptr, 1, lv.ub, lv.ubx,
+                           lv.uby, nullptr);
     });
   }
   if (rnorm)
