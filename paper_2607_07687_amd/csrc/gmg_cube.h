@@ -28,33 +28,39 @@ constexpr int CU_B = 8;                // cube edge
 constexpr int CU_H = 4;                // halo
 constexpr int CU_R = CU_B + 2 * CU_H;  // edge of the loaded region
 constexpr int CU_P = CU_R / 2;         // x-pairs per row
-constexpr int CU_Z = 4;                // planes per thread
-constexpr int CU_NT = CU_P * CU_R * (CU_R / CU_Z);  // 512 threads
+constexpr int CU_G = 4;                // groups of planes, one per thread of a column
+constexpr int CU_NT = CU_P * CU_R * CU_G;  // 512 threads
 
-template <typename T>
+template <typename T, int RZ>
 struct CubeSmem {
-  T x[CU_R][CU_R][CU_R + 2];
+  T x[RZ][CU_R][CU_R + 2];
 };
 
 // VEC = 2 for an even nx (a pair never straddles the edge: 2-wide loads and
-// stores), else 1.
-template <typename T, typename TL, int VEC, bool PROL>
+// stores), else 1.  BZ: planes of the cube, 8 or 4; half cubes where whole ones
+// leave CUs idle, since the half-sweeps' arithmetic is most of a launch (FP64
+// above all, which divides): a launch on 32^3 FP64 takes 8.7 us with halves, 10
+// with whole cubes, on 30x22x18 FP32 7-9 and 8-10.
+template <typename T, typename TL, int VEC, bool PROL, int BZ>
 __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     Geom g, Roles<T> X, int rs, int rd, const T* __restrict__ sigma, const TL* __restrict__ L,
     const T* __restrict__ xc, const uint8_t* __restrict__ active, Geom gc, int cx, int cy, int cz,
     const double* omega_p, const int* done) {
-  __shared__ CubeSmem<T> sm;
+  constexpr int RZ = BZ + 2 * CU_H, CU_Z = RZ / CU_G;  // region planes, planes per thread
+  static_assert(RZ % CU_G == 0, "planes divide among the groups");
+  __shared__ CubeSmem<T, RZ> sm;
   const T* __restrict__ S = X.get(rs);
   T* const W = X.get(rd);
   const int nbx = (g.nx + CU_B - 1) / CU_B, nby = (g.ny + CU_B - 1) / CU_B;
   const int t = xcd_tile(blockIdx.x, gridDim.x);
-  const int i0 = (t % nbx) * CU_B, j0 = (t / nbx) % nby * CU_B, k0 = t / (nbx * nby) * CU_B;
+  const int i0 = (t % nbx) * CU_B, j0 = (t / nbx) % nby * CU_B, k0 = t / (nbx * nby) * BZ;
   // a wave holds eight rows of one parity, so that the colour of a half-sweep
   // picks the same element of every lane's pair
   const int p = threadIdx.x % CU_P, rr = threadIdx.x / CU_P % CU_R;
   const int par = __builtin_amdgcn_readfirstlane(rr / (CU_R / 2));
   const int r = 2 * (rr % (CU_R / 2)) + par;
-  const int z0 = threadIdx.x / (CU_P * CU_R) * CU_Z;  // the thread's first plane of the region
+  // the thread's first plane of the region, the same for a wave
+  const int z0 = __builtin_amdgcn_readfirstlane(threadIdx.x / (CU_P * CU_R)) * CU_Z;
   const int xa = i0 - CU_H + 2 * p, y = j0 - CU_H + r;
   // in-plane offsets of the pair (-1 outside a wall), of the column to its
   // east and of the row above
@@ -144,17 +150,19 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
   }
   __syncthreads();
   // half-sweep h: colour h & 1, the cube grown by 3 - h cells.  Region origins
-  // are even: x + y + z of element e on plane z has the parity of e + par + z.
+  // are even: x + y + z of element e on the thread's plane z has the parity of
+  // e + par + z0 + z, parc that of par + z0.
   auto half = [&](auto hc, auto parc) {
     constexpr int h = decltype(hc)::value;
-    constexpr int lo = 1 + h, hi = CU_R - 1 - h;  // region coordinates updated: [lo, hi)
+    // region coordinates updated: [lo, hi), planes [lo, hz)
+    constexpr int lo = 1 + h, hi = CU_R - 1 - h, hz = RZ - 1 - h;
     if (r < lo || r >= hi) return;
 #pragma unroll
     for (int z = 0; z < CU_Z; ++z) {
       constexpr int SY = CU_R + 2, SZ = CU_R * SY;
       const int e = (decltype(parc)::value + z + h) & 1;  // known at compile time
       const int zr = z0 + z, c = 2 * p + e;
-      if (zr < lo || zr >= hi || c < lo || c >= hi) continue;
+      if (zr < lo || zr >= hz || c < lo || c >= hi) continue;
       T* const q = &sm.x[zr][r][c];
       q[0] = relax_cell<T>(q[0], q[1], q[-1], q[SY], q[-SY], q[SZ], q[-SZ], lx[z][e],
                            e ? lxe[z] : lx[z][1], ly[z][e], lyh[z][e], lz[z][e], lz[z + 1][e],
@@ -170,7 +178,7 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     __syncthreads();
     half(std::integral_constant<int, 3>{}, parc);
   };
-  if (par)
+  if ((par + z0) & 1)
     sweeps(std::integral_constant<int, 1>{});
   else
     sweeps(std::integral_constant<int, 0>{});
@@ -179,7 +187,7 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
 #pragma unroll
   for (int z = 0; z < CU_Z; ++z) {
     const int zr = z0 + z, k = k0 - CU_H + zr;
-    if (zr < CU_H || zr >= CU_H + CU_B || k >= g.nz) continue;
+    if (zr < CU_H || zr >= CU_H + BZ || k >= g.nz) continue;
     const long long q = (long long)k * g.sz + (long long)y * g.sy + xa;
     if constexpr (VEC == 2) {
       if (xa >= g.nx) continue;

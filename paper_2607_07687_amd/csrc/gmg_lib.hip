@@ -1187,12 +1187,20 @@ static void launch_cube(gmg_handle* h, int l, const Roles<T>& X, int rs, int rd,
   const Level& lv = h->lev[l];
   const Geom gc = (xc && l + 1 < h->nlev) ? h->lev[l + 1].g : lv.g;
   const int cx = lv.c[0] ? lv.c[0] : 1, cy = lv.c[1] ? lv.c[1] : 1, cz = lv.c[2] ? lv.c[2] : 1;
-  const dim3 grid(((lv.g.nx + CU_B - 1) / CU_B) * ((lv.g.ny + CU_B - 1) / CU_B) *
-                  ((lv.g.nz + CU_B - 1) / CU_B));
+  const int nxy = ((lv.g.nx + CU_B - 1) / CU_B) * ((lv.g.ny + CU_B - 1) / CU_B);
+  auto go_z = [&](auto vec, auto prol, auto bz) {
+    constexpr int BZ = decltype(bz)::value;
+    hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value, BZ>),
+                       dim3(nxy * ((lv.g.nz + BZ - 1) / BZ)), dim3(CU_NT), 0, h->s, lv.g, X, rs, rd,
+                       sigma, (const TL*)lv.L, xc, lv.active, gc, cx, cy, cz, &h->st->omega, done);
+  };
+  // half cubes while one per CU holds them all
+  const bool halves = nxy * ((lv.g.nz + 3) / 4) <= 256;
   auto go = [&](auto vec, auto prol) {
-    hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value>), grid,
-                       dim3(CU_NT), 0, h->s, lv.g, X, rs, rd, sigma, (const TL*)lv.L, xc,
-                       lv.active, gc, cx, cy, cz, &h->st->omega, done);
+    if (halves)
+      go_z(vec, prol, std::integral_constant<int, 4>{});
+    else
+      go_z(vec, prol, std::integral_constant<int, 8>{});
   };
   auto prol = [&](auto vec) {
     if (xc != nullptr)

@@ -16,7 +16,9 @@ pytestmark = pytest.mark.gpu
 
 CASES = [((8, 8, 8), (False,) * 3), ((9, 7, 17), (False,) * 3), ((16, 24, 4), (True, True, True)),
          ((2, 40, 2), (True, False, True)), ((31, 1, 1), (False,) * 3), ((34, 18, 1), (False,) * 3),
-         ((40, 30, 26), (False, True, False)), ((33, 20, 16), (False, True, True))]
+         ((40, 30, 26), (False, True, False)), ((33, 20, 16), (False, True, True)),
+         # whole cubes (the others are few enough for halves)
+         ((64, 60, 56), (False, True, False)), ((65, 58, 60), (False,) * 3)]
 
 
 @pytest.mark.parametrize("prec,storage", [("f32", "f32"), ("f32", "bf16"), ("f64", "f64")])
