@@ -116,15 +116,16 @@ typedef struct gmg_params {
                             consecutive red-black sweeps of one smoothing step
                             run as one two-sweep pass (temporal blocking: the
                             faces and sigma are read once for both sweeps),
-                            bitwise the same result.  Small levels (up to
-                            2^18 to 2^19 cells, also in FP64 and with an odd
-                            nx) run them on cubes held in LDS, the others as
-                            marching passes, which need FP32 cycles, the
-                            red-black smoother, an even nx and at most 2^28
-                            cells on the level (32-bit buffer offsets);
-                            gmg_autotune and gmg_set_pair_sweeps choose per
-                            level.  The deferred norm's first sweeps stay
-                            passes or single.  0: separate sweeps.            */
+                            bitwise the same result.  Levels of few cubes of
+                            8 x 8 x 8 cells (up to 512; 768 in FP64; 1300 with
+                            an odd nx) run them on cubes held in LDS, the
+                            others as marching passes, which need FP32 cycles,
+                            the red-black smoother, an even nx and at most
+                            2^28 cells on the level (32-bit buffer offsets);
+                            gmg_autotune, gmg_set_pair_sweeps and
+                            gmg_set_cubes choose per level.  With the
+                            deferred norm level 0 runs passes or single
+                            sweeps, never cubes.  0: separate sweeps.         */
   double omega0;         /* relaxation factor at the start of a solve (1.0)   */
   double omega_min;      /* lower bound (0.1)                                 */
   double omega_max;      /* upper bound (1.0)                                 */
@@ -470,18 +471,29 @@ gmg_status gmg_autotune(gmg_handle* h, void* x, const void* sigma, int32_t reps,
 /* Apply a known sweep choice to one level (e.g. from a cache of earlier
  * gmg_autotune runs).  GMG_EINVAL for ty not in {1, 4, 8} (1 or 4 with FP64
  * cycles) or kchunk outside [1, nz].  With ty = 1 on level 0, gmg_solve does
- * not use the deferred norm. */
+ * not use the deferred norm.  On a level whose pairs of sweeps follow the default
+ * rule (no gmg_autotune, gmg_set_pair_sweeps or gmg_set_cubes so far) the call
+ * also turns cubes off, and below level 0 passes: its sweeps run as chosen. */
 gmg_status gmg_set_tiles(gmg_handle* h, int32_t level, int32_t ty, int32_t kchunk);
 
 /* Run the smoothing steps of one level with two-sweep passes on tiles of
  * 64 x ty cells (ty 8 or 16) with kchunk z-planes per workgroup (kchunk = 0:
- * separate sweeps, or two at a time on cubes where pair_sweeps = 1 and the
- * level is small enough for them; ty ignored).  GMG_EINVAL if the handle's parameters do not
- * allow passes (pair_sweeps 0, FP64 cycles, the PCG smoother, an odd nx or
- * more than 2^28 cells on the level),
+ * separate sweeps, ty ignored); turns the level's cubes off.  GMG_EINVAL if the
+ * handle's parameters do not allow passes (pair_sweeps 0, FP64 cycles, the PCG
+ * smoother, an odd nx or more than 2^28 cells on the level),
  * ty is not 8 or 16, or kchunk is outside [0, nz].  Results do not depend on
  * the choice.  Recorded graphs are dropped. */
 gmg_status gmg_set_pair_sweeps(gmg_handle* h, int32_t level, int32_t ty, int32_t kchunk);
+
+/* Run pairs of consecutive sweeps of one level on cubes held in LDS (on = 1),
+ * whatever its passes, or not (on = 0: as gmg_set_pair_sweeps and gmg_set_tiles
+ * chose).  Any size of level; GMG_EINVAL for on = 1 with pair_sweeps 0 or the
+ * PCG smoother.  Results do not depend on the choice.  Recorded graphs are
+ * dropped. */
+gmg_status gmg_set_cubes(gmg_handle* h, int32_t level, int32_t on);
+
+/* *on (host) = 1 if pairs of consecutive sweeps of `level` run on cubes. */
+gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on);
 
 /* Thread-local description of the last error ("" if none). */
 const char* gmg_last_error(void);

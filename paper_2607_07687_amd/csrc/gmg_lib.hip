@@ -836,6 +836,7 @@ struct Level {
                    // with this z-chunk; 0: separate sweeps
   int pair_ty;     // tile rows of the two-sweep pass (8 or 16)
   int cube;        // 1: two consecutive sweeps run on LDS cubes (gmg_cube.h)
+  bool pair_set;   // cube and pair_kc were chosen by a call, not by the default rule
   UBrick* ub;      // uniform-brick map (NULL: off); ubx x uby x ubz bricks
   int ubx, uby, ubz;
   S2TileMode* tm;  // face modes of the two-sweep pass's tiles (NULL: none)
@@ -899,8 +900,10 @@ bool pair_capable(const gmg_params& p, const Geom& g) {
 //            FP64                 33x77x201   1300       56.4 / 67.7
 //                                 79x245x33   1550       67.9 / 68.1
 constexpr long long kCubesPair = 512, kCubesEven = 768, kCubesOdd = 1300;
+// (and whether they may at all, with gmg_set_cubes)
+bool cube_capable(const gmg_params& p) { return p.pair_sweeps && p.smoother == GMG_SMOOTH_RBGS; }
 bool cube_level(const gmg_params& p, const Geom& g) {
-  if (!p.pair_sweeps || p.smoother != GMG_SMOOTH_RBGS) return false;
+  if (!cube_capable(p)) return false;
   const auto edge = [](int n) { return (n + CU_B - 1LL) / CU_B; };
   const long long most = g.nx % 2 ? kCubesOdd : (pair_capable(p, g) ? kCubesPair : kCubesEven);
   return edge(g.nx) * edge(g.ny) * edge(g.nz) <= most;
@@ -1828,6 +1831,7 @@ static gmg_status setup_impl(const gmg_params* p, const void* L, void* stream, g
     // two-sweep passes: by default on every level without cubes (128^3: a pass
     // takes 25-29 us, two fused sweeps 51); the autotuner may choose otherwise
     lv.pair_ty = kPairTYDefault;
+    lv.pair_set = false;
     lv.cube = cube_level(*p, lv.g);
     const bool mapped =
         p->uniform_bricks == 2 || (p->uniform_bricks == 1 && lv.g.n >= kUniformPassCells);
@@ -2679,8 +2683,13 @@ gmg_status gmg_set_tiles(gmg_handle* h, int32_t level, int32_t ty, int32_t kchun
   if ((ty != 1 && ty != 4 && ty != 8) || (h->p.cycle_dtype == GMG_F64 && ty == 8))
     return fail(GMG_EINVAL, "ty must be 1 (split), 4 or 8 (1 or 4 for FP64 cycles)");
   if (kchunk < 1 || kchunk > h->lev[level].g.nz) return fail(GMG_EINVAL, "kchunk out of range");
-  h->lev[level].ty = ty;
-  h->lev[level].kchunk = kchunk;
+  Level& lv = h->lev[level];
+  lv.ty = ty;
+  lv.kchunk = kchunk;
+  if (!lv.pair_set) {  // a level left to the default rule runs the sweeps chosen here
+    lv.cube = 0;
+    if (level > 0) lv.pair_kc = 0;
+  }
   return drop_graphs(h);
 }
 
@@ -2693,12 +2702,32 @@ gmg_status gmg_set_pair_sweeps(gmg_handle* h, int32_t level, int32_t ty, int32_t
                 "two-sweep passes need pair_sweeps = 1, FP32 cycles, the red-black smoother "
                 "and an even nx");
   if (kchunk < 0 || kchunk > h->lev[level].g.nz) return fail(GMG_EINVAL, "kchunk out of range");
-  h->lev[level].cube = kchunk == 0 && cube_level(h->p, h->lev[level].g);
-  h->lev[level].pair_kc = kchunk;
-  if (kchunk != 0) h->lev[level].pair_ty = ty;
+  Level& lv = h->lev[level];
+  lv.cube = 0;
+  lv.pair_set = true;
+  lv.pair_kc = kchunk;
+  if (kchunk != 0) lv.pair_ty = ty;
   refresh_pass_modes(h);
   HIP_TRY(hipGetLastError());
   return drop_graphs(h);
+}
+
+gmg_status gmg_set_cubes(gmg_handle* h, int32_t level, int32_t on) {
+  if (!h) return fail(GMG_EINVAL, "handle is NULL");
+  if (level < 0 || level >= h->nlev) return fail(GMG_EINVAL, "level out of range");
+  if (on != 0 && on != 1) return fail(GMG_EINVAL, "on must be 0 or 1");
+  if (on && !cube_capable(h->p))
+    return fail(GMG_EINVAL, "cubes need pair_sweeps = 1 and the red-black smoother");
+  h->lev[level].cube = on;
+  h->lev[level].pair_set = true;
+  return drop_graphs(h);
+}
+
+gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on) {
+  if (!h || !on) return fail(GMG_EINVAL, "NULL argument");
+  if (level < 0 || level >= h->nlev) return fail(GMG_EINVAL, "level out of range");
+  *on = h->lev[level].cube;
+  return GMG_OK;
 }
 
 gmg_status gmg_autotune(gmg_handle* h, void* x, const void* sigma, int32_t reps,

@@ -136,6 +136,9 @@ _SIGS = [
                                      ctypes.c_int32]),
     ("gmg_set_pair_sweeps", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32,
                                            ctypes.c_int32]),
+    ("gmg_set_cubes", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32]),
+    ("gmg_level_cubes", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32,
+                                       ctypes.POINTER(ctypes.c_int32)]),
     ("gmg_last_error", ctypes.c_char_p, []),
 ]
 
@@ -585,9 +588,20 @@ def gmg_set_tiles(h, level, ty, kchunk):
 
 def gmg_set_pair_sweeps(h, level, kchunk, ty=16):
     """Two-sweep passes on 64 x ty tiles (ty 8 or 16) of kchunk z-planes per
-    workgroup on one level (kchunk 0: separate sweeps, or cubes where the level
-    is small enough)."""
+    workgroup on one level (kchunk 0: separate sweeps); turns its cubes off."""
     _check(load().gmg_set_pair_sweeps(h.ptr, int(level), int(ty), int(kchunk)))
+
+
+def gmg_set_cubes(h, level, on=True):
+    """Pairs of consecutive sweeps of one level on LDS cubes, or as the level's
+    passes and tiles have it."""
+    _check(load().gmg_set_cubes(h.ptr, int(level), int(bool(on))))
+
+
+def gmg_level_cubes(h, level):
+    on = ctypes.c_int32()
+    _check(load().gmg_level_cubes(h.ptr, int(level), ctypes.byref(on)))
+    return bool(on.value)
 
 
 def gmg_batch_autotune(b, reps=5):
