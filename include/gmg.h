@@ -458,9 +458,11 @@ typedef struct gmg_tune_report {
  * {8, 4} and kchunk in {2, 4, ..., 64} up to nz, FP64 cycles: ty 4; and the
  * split half-sweeps, ty 1), and where pair_sweeps allows, `reps` two-sweep
  * passes with ty in {16, 8} and kchunk in {default, 4, 8, ..., 256} (a pass
- * is kept if it beats two of the chosen sweeps and, on small levels, two
- * sweeps on cubes, which stay otherwise: pair_kchunk 0), with
- * HIP events on the handle's stream, and keep the fastest per level.  x and
+ * is kept if it beats two of the chosen sweeps) and on levels that take cubes by
+ * default `reps` pairs on cubes (kept if they beat both; gmg_level_cubes), with
+ * HIP events on the handle's stream, and keep the fastest per level.  The choice
+ * of a level is made again on another handle by gmg_set_tiles,
+ * gmg_set_pair_sweeps with pair_kchunk and gmg_set_cubes, in that order.  x and
  * sigma are level-0 device arrays (dtype == cycle_dtype) used as the sweep's
  * input (x is overwritten with smoothed values; coarse levels use internal
  * buffers).  Recorded graphs are dropped.  report (host) may be NULL.  The
@@ -492,8 +494,10 @@ gmg_status gmg_set_pair_sweeps(gmg_handle* h, int32_t level, int32_t ty, int32_t
  * dropped. */
 gmg_status gmg_set_cubes(gmg_handle* h, int32_t level, int32_t on);
 
-/* *on (host) = 1 if pairs of consecutive sweeps of `level` run on cubes. */
-gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on);
+/* *on (host) = 1 if pairs of consecutive sweeps of `level` run on cubes; *us
+ * (host, may be NULL) = the time of such a pair that the last gmg_autotune
+ * measured (mean without and with the folded correction), 0 if it tried none. */
+gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on, double* us);
 
 /* Thread-local description of the last error ("" if none). */
 const char* gmg_last_error(void);

@@ -836,6 +836,7 @@ struct Level {
                    // with this z-chunk; 0: separate sweeps
   int pair_ty;     // tile rows of the two-sweep pass (8 or 16)
   int cube;        // 1: two consecutive sweeps run on LDS cubes (gmg_cube.h)
+  double us_cube;  // time of two sweeps on cubes that gmg_autotune measured (0: none)
   bool pair_set;   // cube and pair_kc were chosen by a call, not by the default rule
   UBrick* ub;      // uniform-brick map (NULL: off); ubx x uby x ubz bricks
   int ubx, uby, ubz;
@@ -1832,6 +1833,7 @@ static gmg_status setup_impl(const gmg_params* p, const void* L, void* stream, g
     // takes 25-29 us, two fused sweeps 51); the autotuner may choose otherwise
     lv.pair_ty = kPairTYDefault;
     lv.pair_set = false;
+    lv.us_cube = 0.0;
     lv.cube = cube_level(*p, lv.g);
     const bool mapped =
         p->uniform_bricks == 2 || (p->uniform_bricks == 1 && lv.g.n >= kUniformPassCells);
@@ -2099,9 +2101,13 @@ static gmg_status autotune_impl(gmg_handle* h, void* x, const void* sigma, int r
       rep->pair_ty[l] = lv.pair_ty;
       rep->us_pair[l] = 1e3 * pbest;
     }
-    // small levels keep their cubes unless a pass beats them
-    lv.cube = cube_level(h->p, lv.g);
-    if (lv.cube && lv.pair_kc) {
+    // cubes, on the levels that take them by default: kept where they beat both
+    // the pass and two of the chosen sweeps.  A pass kept above stays the
+    // level's choice beside them (level 0 runs it under the deferred norm).
+    lv.cube = 0;
+    lv.us_cube = 0.0;
+    lv.pair_set = true;
+    if (cube_level(h->p, lv.g)) {
       const T* xc = (l + 1 < h->nlev) ? (const T*)h->lev[l + 1].x[0] : nullptr;
       float cost = 0.f;
       for (int fold = 0; fold < 2; ++fold) {
@@ -2115,8 +2121,9 @@ static gmg_status autotune_impl(gmg_handle* h, void* x, const void* sigma, int r
         HIP_TRY(hipEventElapsedTime(&ms, e0, e1));
         cost += ms / reps;
       }
-      lv.cube = 0.5f * cost < 1e-3f * (float)rep->us_pair[l];
-      if (lv.cube) rep->pair_kchunk[l] = 0;
+      const float two = lv.pair_kc ? 1e-3f * (float)rep->us_pair[l] : 2.f * best;
+      lv.cube = 0.5f * cost < two;
+      lv.us_cube = 1e3 * 0.5f * cost;
     }
   }
   (void)hipEventDestroy(e0);
@@ -2723,10 +2730,11 @@ gmg_status gmg_set_cubes(gmg_handle* h, int32_t level, int32_t on) {
   return drop_graphs(h);
 }
 
-gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on) {
+gmg_status gmg_level_cubes(const gmg_handle* h, int32_t level, int32_t* on, double* us) {
   if (!h || !on) return fail(GMG_EINVAL, "NULL argument");
   if (level < 0 || level >= h->nlev) return fail(GMG_EINVAL, "level out of range");
   *on = h->lev[level].cube;
+  if (us) *us = h->lev[level].us_cube;
   return GMG_OK;
 }
 

@@ -138,7 +138,8 @@ _SIGS = [
                                            ctypes.c_int32]),
     ("gmg_set_cubes", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32, ctypes.c_int32]),
     ("gmg_level_cubes", ctypes.c_int, [ctypes.c_void_p, ctypes.c_int32,
-                                       ctypes.POINTER(ctypes.c_int32)]),
+                                       ctypes.POINTER(ctypes.c_int32),
+                                       ctypes.POINTER(ctypes.c_double)]),
     ("gmg_last_error", ctypes.c_char_p, []),
 ]
 
@@ -567,18 +568,21 @@ def gmg_batch_solve_ir(b, xs, sigmas, rtol=1e-10, max_outer=6, max_inner=8, inne
 
 def gmg_autotune(h, x, sigma, reps=5):
     """Time the sweep tile candidates of every level and keep the fastest;
-    also the two-sweep pass where allowed.  Returns per-level dicts (shape,
-    ty, kchunk, us, defaults, pair_kchunk (0: separate sweeps), pair_ty, us_pair)."""
+    also the two-sweep pass where allowed, and cubes on small levels.  Returns
+    per-level dicts (shape, ty, kchunk, us, defaults, pair_kchunk (0: no pass),
+    pair_ty, us_pair, cube (pairs run on cubes), us_cube)."""
     rep = gmg_tune_report()
     xp, sp = h.arrs(h.spec(x, "x", cycle=False), h.spec(sigma, "sigma", cycle=False))
     _check(load().gmg_autotune(h.ptr, xp, sp, int(reps), ctypes.byref(rep)))
     out = []
     for l in range(rep.nlevels):
         n, _ = gmg_level_shape(h, l)
+        cube, us_cube = level_cubes(h, l)
         out.append(dict(level=l, n=n, ty=rep.ty[l], kchunk=rep.kchunk[l], us=rep.us[l],
                         ty_default=rep.ty_default[l], kchunk_default=rep.kchunk_default[l],
                         us_default=rep.us_default[l], pair_kchunk=rep.pair_kchunk[l],
-                        pair_ty=rep.pair_ty[l], us_pair=rep.us_pair[l]))
+                        pair_ty=rep.pair_ty[l], us_pair=rep.us_pair[l], cube=cube,
+                        us_cube=us_cube))
     return out
 
 
@@ -599,9 +603,15 @@ def gmg_set_cubes(h, level, on=True):
 
 
 def gmg_level_cubes(h, level):
-    on = ctypes.c_int32()
-    _check(load().gmg_level_cubes(h.ptr, int(level), ctypes.byref(on)))
-    return bool(on.value)
+    return level_cubes(h, level)[0]
+
+
+def level_cubes(h, level):
+    """(on, us): whether pairs of sweeps of the level run on cubes, and their time
+    as the last gmg_autotune measured it (0: not tried)."""
+    on, us = ctypes.c_int32(), ctypes.c_double()
+    _check(load().gmg_level_cubes(h.ptr, int(level), ctypes.byref(on), ctypes.byref(us)))
+    return bool(on.value), us.value
 
 
 def gmg_batch_autotune(b, reps=5):

@@ -73,3 +73,34 @@ def test_cubes_where_not_allowed():
     G.gmg_smooth(h, 0, xb, sd, 4)
     assert G.gmg_level_cubes(h, 0) and torch.equal(xa, xb)
     h.close()
+
+
+@pytest.mark.parametrize("prec,n", [("f32", (96, 48, 40)), ("f64", (64, 48, 40)),
+                                    ("f32", (65, 33, 24))], ids=str)
+def test_autotune_times_cubes_and_round_trips(prec, n, tmp_path):
+    # every level that takes cubes by default has them timed, against the best
+    # of what else it could run; a handle that is given the cached choices makes
+    # the same ones, and then runs the same deferred decisions
+    from paper_2607_07687_amd import autotune as AT
+    cache = str(tmp_path / "tiles.json")
+    h, sd = handle(prec, n, deferred_norm=1, tail_cells=0)
+    nl = G.gmg_num_levels(h)
+    small = [G.gmg_level_cubes(h, l) for l in range(nl)]
+    rep = AT.tune(h, torch.zeros_like(sd), sd, dtype=prec, storage=prec, cache=cache, reps=3)
+    for l, r in enumerate(rep):
+        say(f"{prec} {n} level {l}: sweep {r['us']:.1f} pass {r['us_pair']:.1f} "
+            f"({r['pair_kchunk']}) cubes {r['us_cube']:.1f} ({r['cube']})")
+        assert small[l] == (r["us_cube"] > 0)
+        if small[l]:
+            other = r["us_pair"] if r["pair_kchunk"] else 2 * r["us"]
+            assert r["cube"] == (r["us_cube"] < other)
+        assert G.gmg_level_cubes(h, l) == r["cube"]
+    h2, _ = handle(prec, n, deferred_norm=1, tail_cells=0)
+    again = AT.tune(h2, torch.zeros_like(sd), sd, dtype=prec, storage=prec, cache=cache)
+    assert all(r["cached"] for r in again)
+    assert [G.gmg_level_cubes(h2, l) for l in range(nl)] == [r["cube"] for r in rep]
+    xa, xb = torch.zeros_like(sd), torch.zeros_like(sd)
+    ra, rb = (G.gmg_solve(a, x, sd, 1e-5, 30) for a, x in ((h, xa), (h2, xb)))
+    assert torch.equal(xa, xb) and ra["history"] == rb["history"]
+    h.close()
+    h2.close()
