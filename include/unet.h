@@ -66,12 +66,23 @@ unet_status unet_conv_fwd(unet_shape s, unet_act x, const void* w, const float* 
  * multiple of 8), 0 for everything else; info[1] = tile width (class 1) or
  * voxel blocks of 16 per wave (class 0); info[2] = output blocks of 16 per
  * wave; info[3] = output-channel groups (workgroups that share an input
- * tile).  3x3x3 convolutions of both classes run the brick or marching kernels,
- * which choose their own tiles; the blocking is that of the gathered kernel (1x1x1
- * taps, or h * w * ld of 2^27 and more).  info: 4 int32 written by the call.
+ * tile).  The blocking is that of the gathered kernel, which 1x1x1 taps run;
+ * unet_conv_launch below tells which kernel a 3x3x3 convolution runs.  info: 4 int32 written by the call.
  * UNET_EINVAL for a bad shape, channel count (cin a multiple of 8 up to 256;
  * cout 16, 32, 64 or 128) or taps. */
 unet_status unet_conv_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
+                             int32_t* info);
+
+/* The kernel that unet_conv_fwd (and unet_conv_dgrad with cin and cout exchanged)
+ * launches for these sizes, x in rows of xld channels (host only, no GPU call):
+ * info[0] = 2 for the marching kernel, 1 for bricks, 0 for gathered operands;
+ * its blocking: info[1] = channels of a chunk and info[2] = chunks staged
+ * together (0 if gathered), info[3] = rows (gathered: blocks of 16 voxels) and
+ * info[4] = blocks of 16 output channels per wave, info[5..6] = waves along w and
+ * h (marching) or along d and the output channels (bricks); info[7] = workgroups
+ * (marching) or work items (bricks).  info: 8 int32 written by the call.
+ * UNET_EINVAL as unet_conv_kernel, and for a bad xld or 2^31 voxels. */
+unet_status unet_conv_launch(unet_shape s, int32_t cin, int32_t xld, int32_t cout, int32_t taps,
                              int32_t* info);
 
 /* Data gradient of a convolution: dx = sum_{o, t} w[o][t][c] dy[v - t + 1][o]
@@ -82,7 +93,7 @@ unet_status unet_conv_dgrad(unet_shape s, unet_act dy, const void* w, int32_t ta
 
 /* The same with the ReLU backward of dx's own layer in the same pass: dx is
  * zero where y (its forward output, dx.c channels) is not positive, bitwise as
- * unet_conv_dgrad followed by unet_relu_bwd. */
+ * unet_conv_dgrad followed by unet_relu_bwd.  y must not overlap dx. */
 unet_status unet_conv_dgrad_relu(unet_shape s, unet_act dy, const void* w, int32_t taps, unet_act y,
                                  unet_act dx, void* wflip, void* stream);
 
@@ -107,7 +118,7 @@ unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps,
  * 2^30 and more, or 2^31 voxels) runs the voxel-chunk kernel.  info: 6 int32
  * written by the call.  UNET_EINVAL for a bad shape, channel count or taps. */
 unet_status unet_wgrad_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
-                              int32_t* info);
+                               int32_t* info);
 
 /* dy_pre = dy * (y > 0) (ReLU backward, in place on dy allowed). */
 unet_status unet_relu_bwd(unet_shape s, unet_act y, unet_act dy, unet_act out, void* stream);

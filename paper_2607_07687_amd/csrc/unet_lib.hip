@@ -849,9 +849,9 @@ long long wgrad_chunk(long long nvox) {
 //                multiple of 8.
 //   CONV_GATHER: everything else.
 // Both with a blocking that splits the output channels while the grid would
-// leave CUs without work.  The gathered kernel (1x1x1 taps; planes too large
-// for the brick kernel's 32-bit offsets) runs that blocking, in class
-// CONV_TILE with 64 voxels per wave.
+// leave CUs without work.  The gathered kernel (1x1x1 taps; grids where
+// conv_choice picks it) runs that blocking, in class CONV_TILE with 64 voxels per
+// wave.
 enum { CONV_GATHER = 0, CONV_TILE = 1 };
 struct ConvPlan {
   int kind, mb, nb, tw;
@@ -933,6 +933,7 @@ constexpr bool brick_exists(int shape, int ck, int nc, int nb) {
 struct BrickPlan {
   int ck, nc, shape, nb;  // shape < 0: no brick kernel for these sizes
   int nbw, nbh, nbd;
+  double us;  // estimated time
 };
 
 // The instance with the least estimated time (work items in rounds of 256 CUs,
@@ -956,7 +957,7 @@ BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
       const double t = std::ceil(items / 256.0) * kBrickUs[nb - 1][sh][brick_class(ck, nc)];
       if (items < 2e9 && (best.shape < 0 || t < tbest)) {
         tbest = t;
-        best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd};
+        best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd, 3 + t * (nc == 1 ? cin / ck : 1)};
       }
     }
   }
@@ -1018,45 +1019,116 @@ void enq_brick(const BrickPlan& p, ConvArgs a, int cout, hipStream_t st) {
   }
 }
 
-// Enqueues the marching kernel if it takes these sizes and is the faster one:
-// from 9 planes per CU on, its two steps of start and its larger tiles pay off.
-// Marching against bricks, us (planes per CU): 8 -> 16 on 2 x 128^3 (32) 49 / 61,
-// on 48x56x104 (3) 11.1 / 10.7; 16 -> 16 on 2 x 128^3 72 / 91, 100x90x120 (9) 27.7 /
-// 28.7, 48x56x104 15.5 / 11.5; 16 -> 32 on 2 x 128^3 135 / 166, 2 x 64^3 (8) 22.8 /
-// 22.7; 32 -> 16 on 2 x 128^3 131 / 158, 100x90x120 42.8 / 43.7, 64^3 (2) 15.4 / 11.9;
-// 32 -> 32 on 2 x 64^3 (8) 37.5 / 36.4, 32 -> 64 (16) 64.5 / 68.3.
-template <typename K>
-bool enq_march(ConvArgs a, int cout, hipStream_t st, K) {
-  if (cout / 16 % K::NB) return false;
-  a.nbw = (a.s.w + 16 * K::WW - 1) / (16 * K::WW);
-  a.nbh = (a.s.h + K::MB * K::WH - 1) / (K::MB * K::WH);
-  const long long steps = (long long)a.s.n * a.nbw * a.nbh * a.s.d;
-  const int groups = cout / 16 / K::NB;
-  const long long nchunk = std::min(steps, std::max(1LL, 256LL * K::PER_CU / groups));
-  if (steps * groups < 9 * 256) return false;
-  a.q = (int)(steps / nchunk);
-  a.r = (int)(steps % nchunk);
-  const dim3 grid((unsigned)nchunk, (unsigned)groups);
-  if constexpr (K::CK > 8)
-    if (a.gate) {
-      hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, true>), grid,
-                         dim3(K::NT), 0, st, a);
-      return true;
-    }
-  hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, false>), grid,
-                     dim3(K::NT), 0, st, a);
-  return true;
+// The marching kernel's instance for these channels, as f(March<...>{}); false if
+// it has none.
+template <typename F>
+bool with_march(int cin, int cout, F&& f) {
+  if (cin == 8) return f(unet::March<8, 1, 8, 2, 2>{});
+  if (cin == 16)
+    return cout % 32 ? f(unet::March<16, 1, 8, 2, 2>{}) : f(unet::March<16, 2, 4, 2, 2>{});
+  return cin == 32 && f(unet::March<32, 1, 4, 2, 4>{});
 }
 
-bool march(const ConvArgs& a, int cout, hipStream_t st) {
+struct MarchPlan {
+  int nbw, nbh, groups;
+  long long steps, nchunk;  // nchunk 0: no marching kernel for these sizes
+  double us;                // estimated time
+};
+
+// The marching kernel's launch and estimated time: one step more than a
+// workgroup's share, of 2.6 to 4 us each (less where the tile reaches past the
+// grid).  Against bricks, us (in brackets the estimates): 8 -> 16 on 2 x 128^3 49 /
+// 61 (48 / 70), on 48x56x104 11.1 / 10.7; 16 -> 16 on 2 x 128^3 72 / 91 (72 / 93),
+// 100x90x120 27.7 / 28.7, 48x56x104 15.5 / 11.5; 16 -> 32 on 2 x 128^3 135 / 166 (136
+// / 157), 2 x 64^3 22.8 / 22.7; 32 -> 16 on 2 x 128^3 131 / 158 (131 / 153),
+// 100x90x120 42.8 / 43.7, 64^3 15.4 / 11.9; 32 -> 32 on 2 x 64^3 37.5 / 36.4, 32 ->
+// 64 64.5 / 68.3.  Flat grids, where a brick's other planes lie outside: 16 -> 16
+// on 512 x 512 9.9 / 15.3, 16 -> 32 on 8 x 256 x 256 22 / 43.  Narrow ones, where
+// most of a tile does: 32 -> 32 on 4096 x 8 x 8 84 / 29, 16 -> 16 on 4096 x 16 x 16
+// 34 / 24.
+MarchPlan march_plan(unet_shape s, int cin, int xld, int cout) {
+  MarchPlan p{};
   // offsets within a plane are 32-bit
-  if ((long long)a.s.h * a.s.w * a.xld >= (1LL << 30) - 64) return false;
-  if (a.cin == 8) return enq_march(a, cout, st, unet::March<8, 1, 8, 2, 2>{});
-  if (a.cin == 16)
-    return cout % 32 ? enq_march(a, cout, st, unet::March<16, 1, 8, 2, 2>{})
-                     : enq_march(a, cout, st, unet::March<16, 2, 4, 2, 2>{});
-  if (a.cin == 32) return enq_march(a, cout, st, unet::March<32, 1, 4, 2, 4>{});
-  return false;
+  if ((long long)s.h * s.w * xld >= (1LL << 30) - 64) return p;
+  with_march(cin, cout, [&](auto kc) {
+    using K = decltype(kc);
+    if (cout / 16 % K::NB) return false;
+    const int tw = 16 * K::WW, th = K::MB * K::WH;
+    p.nbw = (s.w + tw - 1) / tw;
+    p.nbh = (s.h + th - 1) / th;
+    p.steps = (long long)s.n * p.nbw * p.nbh * s.d;
+    p.groups = cout / 16 / K::NB;
+    p.nchunk = std::min(p.steps, std::max(1LL, 256LL * K::PER_CU / p.groups));
+    const double used = (double)s.w * s.h / ((double)p.nbw * tw * p.nbh * th);
+    const double us = cin == 8 ? (p.groups > 1 ? 3.3 : 2.6) : (cin == 16 ? 4.0 : 3.85);
+    p.us = 4 + (std::ceil((double)p.steps / p.nchunk) + 1) * us * (0.7 + 0.3 * used);
+    return true;
+  });
+  return p;
+}
+
+void enq_march(const MarchPlan& p, ConvArgs a, int cout, hipStream_t st) {
+  a.nbw = p.nbw;
+  a.nbh = p.nbh;
+  a.q = (int)(p.steps / p.nchunk);
+  a.r = (int)(p.steps % p.nchunk);
+  const dim3 grid((unsigned)p.nchunk, (unsigned)p.groups);
+  with_march(a.cin, cout, [&](auto kc) {
+    using K = decltype(kc);
+    if constexpr (K::CK > 8)
+      if (a.gate) {
+        hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, true>), grid,
+                           dim3(K::NT), 0, st, a);
+        return true;
+      }
+    hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, false>), grid,
+                       dim3(K::NT), 0, st, a);
+    return true;
+  });
+}
+
+// Estimated time (us) of the gathered kernel: rounds of workgroups over its K
+// steps, a latency each at least, and its 2-byte stores.  Measured on grids that
+// waste a brick: 128 -> 128 channels on 256 x 256 x 1 170 (estimate 158), on
+// 256 x 256 x 2 330 (309); 64 -> 64 80 (64) and 114 (121); 16 -> 16 17 and 20 (19).
+double gather_us(unet_shape s, int cin, int cout) {
+  const ConvPlan p = conv_plan(s, cin, cout, 27);
+  const double steps = (27 * cin + 31) / 32;
+  const double rounds = std::ceil((double)p.grid * (cout / 16 / p.nb) / 256);
+  // per step and round, by output blocks; rows of 128 bytes and more fall out of the L1
+  constexpr double kUs[2][4] = {{0.25, 0.33, 0.45, 0.7}, {0.5, 0.6, 0.85, 1.2}};
+  double least = 0.6, us = kUs[cin >= 64][p.nb == 8 ? 3 : p.nb / 2];
+  if (p.mb == 1) {  // (of a single column two taps of three load nothing new)
+    least = 0.3;
+    us = p.nb == 2 ? 0.28 : (s.w == 1 ? 0.07 : 0.2);
+  }
+  return 8 + steps * std::max(least, rounds * us) + (double)nvox_of(s) * cout * 2 / 0.8e6;
+}
+
+// The kernel of a convolution: the one of least estimated time, within margins
+// for what the estimates miss.  Gathering is the faster one where a brick is
+// mostly padding: 128 -> 128 channels on 256 x 256 x 1 170 us against 838 on
+// bricks, on 128 x 128 x 4 172 / 212 (128 x 128 x 6: 337 / 214); 16 -> 16 on
+// 256 x 256 x 2 19.7 / 21.4.  On 1800 random grids of 1 to 512 voxels a side the
+// choice was the fastest kernel or within 10% of it but for grids one or two
+// voxels wide or tens of microseconds short.
+enum { CONV_GATHERED = 0, CONV_BRICK = 1, CONV_MARCH = 2 };
+struct ConvChoice {
+  int kernel;
+  BrickPlan brick;
+  MarchPlan march;
+};
+
+ConvChoice conv_choice(unet_shape s, int cin, int xld, int cout, int taps) {
+  ConvChoice c{};
+  if (taps != 27) return c;
+  c.brick = brick_plan(s, cin, xld, cout);
+  c.march = march_plan(s, cin, xld, cout);
+  double us = gather_us(s, cin, cout);
+  if (c.brick.shape >= 0 && (s.w <= 2 ? 1.0 : 0.8) * c.brick.us <= us)
+    c.kernel = CONV_BRICK, us = c.brick.us;
+  if (c.march.nchunk > 0 && c.march.us < 0.95 * us) c.kernel = CONV_MARCH;
+  return c;
 }
 
 // Rows of workspace past the chunks' (part of the size callers allocate).
@@ -1243,33 +1315,34 @@ static unet_status conv(unet_shape s, unet_act x, const void* w, const float* bi
   if (ob != 1 && ob != 2 && ob != 4 && ob != 8)
     return ufail(UNET_EINVAL, "output channels must be 16, 32, 64 or 128");
   hipStream_t st = (hipStream_t)stream;
-  if (taps == 27) {
-    const BrickPlan bp = brick_plan(s, x.c, x.ld, y.c);
-    if (bp.shape >= 0) {
-      ConvArgs a{};
-      a.s = s;
-      a.x = (const uint16_t*)x.p;
-      a.xld = x.ld;
-      a.xoff = x.off;
-      a.cin = x.c;
-      a.w = (const uint16_t*)w;
-      a.bias = bias;
-      a.y = (uint16_t*)y.p;
-      a.yld = y.ld;
-      a.yoff = y.off;
-      a.yf = out_f32;
-      a.relu = relu;
-      a.wide = (uintptr_t)(out_f32 ? (void*)out_f32 : y.p) % 16 == 0;
-      if (gate) {
-        a.gate = (const uint16_t*)gate->p;
-        a.gld = gate->ld;
-        a.goff = gate->off;
-        a.wide = a.wide && (uintptr_t)gate->p % 16 == 0;
-      }
-      if (!march(a, y.c, st)) enq_brick(bp, a, y.c, st);
-      UHIP(hipGetLastError());
-      return UNET_OK;
+  const ConvChoice ch = conv_choice(s, x.c, x.ld, y.c, taps);
+  if (ch.kernel != CONV_GATHERED) {
+    ConvArgs a{};
+    a.s = s;
+    a.x = (const uint16_t*)x.p;
+    a.xld = x.ld;
+    a.xoff = x.off;
+    a.cin = x.c;
+    a.w = (const uint16_t*)w;
+    a.bias = bias;
+    a.y = (uint16_t*)y.p;
+    a.yld = y.ld;
+    a.yoff = y.off;
+    a.yf = out_f32;
+    a.relu = relu;
+    a.wide = (uintptr_t)(out_f32 ? (void*)out_f32 : y.p) % 16 == 0;
+    if (gate) {
+      a.gate = (const uint16_t*)gate->p;
+      a.gld = gate->ld;
+      a.goff = gate->off;
+      a.wide = a.wide && (uintptr_t)gate->p % 16 == 0;
     }
+    if (ch.kernel == CONV_MARCH)
+      enq_march(ch.march, a, y.c, st);
+    else
+      enq_brick(ch.brick, a, y.c, st);
+    UHIP(hipGetLastError());
+    return UNET_OK;
   }
   const ConvPlan p = conv_plan(s, x.c, y.c, taps);
   const uint16_t* xp = (const uint16_t*)x.p;
@@ -1312,6 +1385,36 @@ unet_status unet_conv_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t ta
   info[1] = p.kind == CONV_GATHER ? p.mb : p.tw;
   info[2] = p.nb;
   info[3] = cout / 16 / p.nb;
+  return UNET_OK;
+}
+
+unet_status unet_conv_launch(unet_shape s, int32_t cin, int32_t xld, int32_t cout, int32_t taps,
+                             int32_t* info) {
+  if (!info || !shape_ok(s) || cin <= 0 || cin % 8 || cin > 256 || xld < cin || xld % 8 ||
+      (taps != 27 && taps != 1) || (cout != 16 && cout != 32 && cout != 64 && cout != 128) ||
+      nvox_of(s) >= (1LL << 31))
+    return ufail(UNET_EINVAL, "bad conv_launch args");
+  const ConvChoice c = conv_choice(s, cin, xld, cout, taps);
+  std::fill(info, info + 8, 0);
+  info[0] = c.kernel;
+  if (c.kernel == CONV_MARCH) {
+    with_march(cin, cout, [&](auto kc) {
+      using K = decltype(kc);
+      info[1] = K::CK, info[2] = 1, info[3] = K::MB, info[4] = K::NB, info[5] = K::WW,
+      info[6] = K::WH;
+      return true;
+    });
+    info[7] = (int32_t)(c.march.nchunk * c.march.groups);
+  } else if (c.kernel == CONV_BRICK) {
+    const BrickShape& b = kBricks[c.brick.shape];
+    info[1] = c.brick.ck, info[2] = c.brick.nc, info[3] = b.mb, info[4] = c.brick.nb,
+    info[5] = b.wd, info[6] = b.wc;
+    info[7] = (int32_t)((long long)s.n * c.brick.nbw * c.brick.nbh * c.brick.nbd *
+                        (cout / 16 / c.brick.nb / b.wc));
+  } else {
+    const ConvPlan p = conv_plan(s, cin, cout, taps);
+    info[3] = p.mb, info[4] = p.nb;
+  }
   return UNET_OK;
 }
 

@@ -43,6 +43,7 @@ _SIGS = [
     ("unet_wgrad_workspace", ctypes.c_size_t, [unet_shape, _I, _I, _I]),
     ("unet_conv_wgrad", ctypes.c_int, [unet_shape, unet_act, unet_act, _I, _V, _V, _V, _V]),
     ("unet_wgrad_kernel", ctypes.c_int, [unet_shape, _I, _I, _I, _V]),
+    ("unet_conv_launch", ctypes.c_int, [unet_shape, _I, _I, _I, _I, _V]),
     ("unet_conv_kernel", ctypes.c_int, [unet_shape, _I, _I, _I, _V]),
     ("unet_relu_bwd", ctypes.c_int, [unet_shape, unet_act, unet_act, unet_act, _V]),
     ("unet_pool_fwd", ctypes.c_int, [unet_shape, unet_act, unet_act, _V]),
@@ -151,6 +152,20 @@ def unet_conv_kernel(s, cin, cout, taps):
     out = {"kind": kind, "nb": info[2], "groups": info[3]}
     out["mb" if kind == "gather" else "tw"] = info[1]
     return out
+
+
+def unet_conv_launch(s, cin, cout, taps, xld=None):
+    """The kernel unet_conv_fwd launches (host only): ("march", chunk, rows, blocks,
+    waves along w, along h), ("brick", chunk, chunks, rows, blocks, waves along d,
+    along the channels) or ("gather", voxel blocks, output blocks)."""
+    info = (ctypes.c_int32 * 8)()
+    _check(load().unet_conv_launch(s, cin, xld or cin, cout, taps,
+                                   ctypes.cast(info, ctypes.c_void_p)))
+    if info[0] == 2:
+        return ("march", info[1], info[3], info[4], info[5], info[6])
+    if info[0] == 1:
+        return ("brick",) + tuple(info[1:7])
+    return ("gather", info[3], info[4])
 
 
 def unet_wgrad_kernel(s, cin, cout, taps):

@@ -1,0 +1,80 @@
+"""Host-side choice of the convolution kernels, from unet_conv_launch (no GPU
+call): grids that waste a brick or a marching tile take another kernel, those
+that fill them do not."""
+import random
+
+import pytest
+
+from paper_2607_07687_amd import unet as UN
+from tests.test_gpu_unet_dispatch import CONV
+
+
+def conv(n, d, h, w, cin, cout):
+    return UN.unet_conv_launch(UN.shape(n, d, h, w), cin, cout, 27)
+
+
+@pytest.mark.parametrize("dhw,cin,cout", [((1, 512, 512), 8, 16), ((1, 512, 512), 16, 16),
+                                          ((1, 512, 512), 16, 32), ((1, 512, 512), 32, 16)])
+def test_flat_grids_march(dhw, cin, cout):
+    # one plane: a brick's other planes lie outside the grid
+    assert conv(1, *dhw, cin, cout)[0] == "march"
+    assert conv(8, 1, 256, 256, cin, cout)[0] == "march"
+
+
+@pytest.mark.parametrize("cin,cout", [(16, 16), (32, 32), (64, 64), (128, 128), (64, 128)])
+def test_columns_are_gathered(cin, cout):
+    # a single column of w: 15 of a brick's 16 voxels lie outside
+    assert conv(1, 256, 256, 1, cin, cout)[0] == "gather"
+
+
+@pytest.mark.parametrize("d,h,w", [(4096, 8, 8), (4096, 16, 16)])
+@pytest.mark.parametrize("cin,cout", [(8, 16), (16, 16), (32, 16), (32, 32)])
+def test_narrow_grids_do_not_march(d, h, w, cin, cout):
+    # a marching tile is 32 voxels wide
+    assert conv(1, d, h, w, cin, cout)[0] == "brick"
+
+
+@pytest.mark.parametrize("cin,cout,m,kernel", [
+    (8, 16, 128, "march"), (16, 16, 128, "march"), (32, 16, 128, "march"), (16, 32, 64, "brick"),
+    (32, 32, 64, "brick"), (64, 32, 64, "brick"), (32, 64, 32, "brick"), (64, 64, 32, "brick"),
+    (128, 64, 32, "brick"), (64, 128, 16, "brick"), (128, 128, 16, "brick")])
+def test_unet_levels(cin, cout, m, kernel):
+    # the layers of a 2 x 128^3 training step, forward and data gradient
+    assert conv(2, m, m, m, cin, cout)[0] == kernel
+    if cin >= 16:
+        assert conv(2, m, m, m, cout, cin)[0] in ("march", "brick")
+
+
+def test_one_tap_is_gathered():
+    assert UN.unet_conv_launch(UN.shape(2, 64, 64, 64), 16, 16, 1)[0] == "gather"
+
+
+def test_bad_arguments():
+    s = UN.shape(1, 8, 8, 8)
+    for args in ((s, 12, 16, 27), (s, 16, 48, 27), (s, 16, 16, 9), (s, 16, 16, 27, 8),
+                 (UN.shape(1, 0, 8, 8), 16, 16, 27)):
+        with pytest.raises(UN.UNetError):
+            UN.unet_conv_launch(*args)
+
+
+def sizes(seed, count):
+    """Grids from single voxels to 2^22, flat, narrow and whole ones."""
+    r = random.Random(seed)
+    while count:
+        n, (d, h, w) = r.choice((1, 2, 4)), (int(2 ** r.uniform(0, 9)) for _ in range(3))
+        if n * d * h * w <= 1 << 22:
+            count -= 1
+            yield n, d, h, w
+
+
+def test_cases_cover_every_convolution_instance():
+    # every instance that a grid can choose, for every channel count of a layer,
+    # is run against the FP64 sums by a case of the GPU tests
+    seen = {conv(*c) for c in CONV}
+    for g in sizes(1, 4000):
+        for cin in (8, 16, 32, 64, 128):
+            for cout in (16, 32, 64, 128):
+                k = conv(*g, cin, cout)
+                assert k in seen, (k, g, cin, cout)
+    assert len([k for k in seen if k[0] == "brick"]) == 21
+    assert len([k for k in seen if k[0] == "march"]) == 4
