@@ -223,11 +223,12 @@ __global__ __launch_bounds__(64 * WD * WC)
   // Staging: a thread keeps one piece of the slots it stages, SPI apart.  Raw
   // buffer loads from the plane below the brick: an offset at or past the
   // descriptor's size reads zero and touches no memory, which gives the zeros
-  // outside the grid (the host keeps SD planes below 2^31 bytes).
+  // outside the grid (the host keeps SD planes below 2^31 bytes; unsigned, as the
+  // offsets of slots outside the grid may wrap).
   constexpr int kOut = 0x7FFFFFF0;
   constexpr int SPI = B::SPI;
   const int sp = tid % Q8, s0 = tid / Q8;
-  const int rw = W * a.xld * 2, pl = H * rw, vx = a.xld * 2;
+  const unsigned rw = W * a.xld * 2, pl = H * rw, vx = a.xld * 2;
   uint4 v[NIT];
   const int passes = B::KP ? 3 : a.cin / CK;
   auto fetch = [&](const Item& t, int ps) {
@@ -235,7 +236,7 @@ __global__ __launch_bounds__(64 * WD * WC)
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
         (void*)(a.x + (((long long)t.n0 * D + dlow) * plane) * a.xld + a.xoff), 0, kOut, 0x00020000);
     int col = s0 % SW, row = (s0 / SW) % SH, sd = s0 / (SW * SH);
-    int off = sd * pl + (t.h0 - 1 + row) * rw + (t.w0 - 1 + col) * vx + sp * 16;
+    unsigned off = sd * pl + (t.h0 - 1 + row) * rw + (t.w0 - 1 + col) * vx + sp * 16;
 #pragma unroll
     for (int it = 0; it < NIT; ++it) {
       const bool in = (unsigned)(dlow + sd) < (unsigned)D &&
@@ -416,7 +417,9 @@ struct March {
   static_assert(PER_CU * 4 * PB * 16 <= 160 * 1024, "four planes in LDS");
 };
 
-template <int CK, int NB, int MB, int WW, int WH, bool GATE>
+// FAR: planes of 2^31 bytes and more, whose offsets count from the row below the
+// tile (a variant of its own: the plane's start as base is 0.5% faster).
+template <int CK, int NB, int MB, int WW, int WH, bool GATE, bool FAR>
 __global__ __launch_bounds__(64 * WW * WH, 2) void k_conv_march(ConvArgs a) {
   using B = March<CK, NB, MB, WW, WH>;
   constexpr int NT = B::NT, SW = B::SW, P8 = B::P8, TPS = B::TPS, STEPS = B::STEPS, NIT = B::NIT,
@@ -483,15 +486,16 @@ __global__ __launch_bounds__(64 * WW * WH, 2) void k_conv_march(ConvArgs a) {
       const int e = tid + i * NT, slot = e / P8, row = slot / SW, col = slot % SW;
       const int h = s.h0 - 1 + row, w = s.w0 - 1 + col;
       xo[i] = slot < B::SLOTS && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W
-                  ? ((h * W + w) * a.xld + ((e % P8) ^ swz(col)) * 8) * 2
+                  ? (((FAR ? row : h) * W + w) * a.xld + ((e % P8) ^ swz(col)) * 8) * 2
                   : kOut;
     }
     return s;
   };
   const long long plane = (long long)H * W;
   auto fetch = [&](const Step& s, uint4 (&v)[NIT]) {
+    const long long below = FAR ? (s.h0 - 1LL) * W : 0;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.x + ((long long)s.n * D + s.p) * plane * a.xld + a.xoff), 0,
+        (void*)(a.x + (((long long)s.n * D + s.p) * plane + below) * a.xld + a.xoff), 0,
         (unsigned)s.p < (unsigned)D ? kOut : 0, 0x00020000);
 #pragma unroll
     for (int i = 0; i < NIT; ++i)

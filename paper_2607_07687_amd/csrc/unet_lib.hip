@@ -936,6 +936,12 @@ struct BrickPlan {
   double us;  // estimated time
 };
 
+// Whether the byte offsets of `planes` whole planes and `rows` rows of xld channels
+// stay within a staging descriptor's 2^31.
+bool offsets_fit(int planes, int rows, unet_shape s, int xld) {
+  return ((double)planes * s.h + rows) * s.w * xld * 2 < (double)((1LL << 31) - 4096);
+}
+
 // The instance with the least estimated time (work items in rounds of 256 CUs,
 // times kBrickUs): the fastest one on the grids measured, or within 8 % of it.
 // Every instance gives bitwise the same result (8 to 128 channels in powers of
@@ -943,8 +949,6 @@ struct BrickPlan {
 BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
   BrickPlan best{};
   best.shape = -1;
-  // staging offsets and work items are 32-bit
-  if ((long long)8 * s.h * s.w * xld * 2 >= (1LL << 31) - 16) return best;
   int ck, nc;
   brick_chunks(cin, &ck, &nc);
   double tbest = 0.0;
@@ -952,6 +956,8 @@ BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
     const BrickShape& b = kBricks[sh];
     for (int nb = 1; nb <= 2; ++nb) {
       if (!brick_exists(sh, ck, nc, nb) || (cout / 16) % (nb * b.wc)) continue;
+      // staging offsets (and work items, below) are 32-bit
+      if (!offsets_fit(nc > 1 ? b.wd : b.wd + 2, 0, s, xld)) continue;
       const int nbw = (s.w + 15) / 16, nbh = (s.h + b.mb - 1) / b.mb, nbd = (s.d + b.wd - 1) / b.wd;
       const double items = (double)s.n * nbw * nbh * nbd * (cout / 16 / nb / b.wc);
       const double t = std::ceil(items / 256.0) * kBrickUs[nb - 1][sh][brick_class(ck, nc)];
@@ -1032,6 +1038,7 @@ bool with_march(int cin, int cout, F&& f) {
 struct MarchPlan {
   int nbw, nbh, groups;
   long long steps, nchunk;  // nchunk 0: no marching kernel for these sizes
+  bool far;                 // planes past a descriptor's reach
   double us;                // estimated time
 };
 
@@ -1048,12 +1055,12 @@ struct MarchPlan {
 // 34 / 24.
 MarchPlan march_plan(unet_shape s, int cin, int xld, int cout) {
   MarchPlan p{};
-  // offsets within a plane are 32-bit
-  if ((long long)s.h * s.w * xld >= (1LL << 30) - 64) return p;
   with_march(cin, cout, [&](auto kc) {
     using K = decltype(kc);
     if (cout / 16 % K::NB) return false;
     const int tw = 16 * K::WW, th = K::MB * K::WH;
+    p.far = !offsets_fit(1, 0, s, xld);
+    if (p.far && !offsets_fit(0, th + 2, s, xld)) return false;
     p.nbw = (s.w + tw - 1) / tw;
     p.nbh = (s.h + th - 1) / th;
     p.steps = (long long)s.n * p.nbw * p.nbh * s.d;
@@ -1075,14 +1082,25 @@ void enq_march(const MarchPlan& p, ConvArgs a, int cout, hipStream_t st) {
   const dim3 grid((unsigned)p.nchunk, (unsigned)p.groups);
   with_march(a.cin, cout, [&](auto kc) {
     using K = decltype(kc);
-    if constexpr (K::CK > 8)
-      if (a.gate) {
-        hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, true>), grid,
-                           dim3(K::NT), 0, st, a);
-        return true;
-      }
-    hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH, false>), grid,
-                       dim3(K::NT), 0, st, a);
+    auto go = [&](auto gate, auto far) {
+      hipLaunchKernelGGL((unet::k_conv_march<K::CK, K::NB, K::MB, K::WW, K::WH,
+                                             decltype(gate)::value, decltype(far)::value>),
+                         grid, dim3(K::NT), 0, st, a);
+    };
+    auto go_far = [&](auto gate) {
+      if (p.far)
+        go(gate, std::true_type{});
+      else
+        go(gate, std::false_type{});
+    };
+    if constexpr (K::CK > 8) {  // gates come with gradients, of 16 channels and more
+      if (a.gate)
+        go_far(std::true_type{});
+      else
+        go_far(std::false_type{});
+    } else {
+      go_far(std::false_type{});
+    }
     return true;
   });
 }

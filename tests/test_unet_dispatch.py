@@ -45,6 +45,17 @@ def test_unet_levels(cin, cout, m, kernel):
         assert conv(2, m, m, m, cout, cin)[0] in ("march", "brick")
 
 
+@pytest.mark.parametrize("dhw,cin,cout,kernel", [
+    ((1, 2048, 2048), 32, 16, "march"), ((3, 2048, 2048), 64, 64, "brick"),
+    ((1, 8192, 8192), 16, 16, "march"), ((1, 4000, 4096), 64, 32, "brick"),
+    ((1, 4096, 2000), 128, 32, "brick"), ((64, 2048, 2048), 8, 16, "march")])
+def test_large_planes_are_staged(dhw, cin, cout, kernel):
+    # planes of 2^27 elements and more: several of them, or one, span 2^31 bytes
+    assert conv(1, *dhw, cin, cout)[0] == kernel
+    # out of a descriptor's reach: a tile's rows, a brick's planes
+    assert conv(1, 1, 16, 1 << 24, cin, cout)[0] == "gather"
+
+
 def test_one_tap_is_gathered():
     assert UN.unet_conv_launch(UN.shape(2, 64, 64, 64), 16, 16, 1)[0] == "gather"
 
