@@ -111,14 +111,20 @@ unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps,
  * multiple of 4, 8 or a multiple of 16 input channels), which take any multiple
  * of 16 output channels, else 0 (16, 32, 64 or 128); info[1..3] = input
  * channels, output channels and w extent of a chunk's part (class 1, 0
- * otherwise); info[4] = number of chunks (partial rows of the workspace);
- * info[5] = d planes per chunk (class 1).  3x3x3 taps on 8 or a multiple of 16
- * input channels run the tiled kernel in both classes, which divides the grid
- * in its own way and writes at most that many rows; the rest (and h * w * ld of
- * 2^30 and more, or 2^31 voxels) runs the voxel-chunk kernel.  info: 6 int32
- * written by the call.  UNET_EINVAL for a bad shape, channel count or taps. */
+ * otherwise); info[4] = number of chunks; info[5] = d planes per chunk (class 1).
+ * unet_wgrad_launch below tells which kernel runs: the tiled one divides the grid
+ * in its own way.  info: 6 int32 written by the call.  UNET_EINVAL for a bad shape, channel count or taps. */
 unet_status unet_wgrad_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
                                int32_t* info);
+
+/* The kernel that unet_conv_wgrad launches for these sizes, x and dy in rows of
+ * xld and dld channels (host only, no GPU call): info[0] = 1 for the tiled
+ * kernel, 0 for voxel chunks; of the tiled kernel info[1..2] = input and output
+ * channels of a workgroup, info[3] = octets of voxels along w of its tile,
+ * info[4] = shares (partial rows written), info[5] = channel parts.  info: 6 int32
+ * written by the call.  UNET_EINVAL as unet_wgrad_kernel, and for a bad ld. */
+unet_status unet_wgrad_launch(unet_shape s, int32_t cin, int32_t xld, int32_t cout, int32_t dld,
+                              int32_t taps, int32_t* info);
 
 /* dy_pre = dy * (y > 0) (ReLU backward, in place on dy allowed). */
 unet_status unet_relu_bwd(unet_shape s, unet_act y, unet_act dy, unet_act out, void* stream);

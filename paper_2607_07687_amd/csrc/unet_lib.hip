@@ -1149,9 +1149,6 @@ ConvChoice conv_choice(unet_shape s, int cin, int xld, int cout, int taps) {
   return c;
 }
 
-// Rows of workspace past the chunks' (part of the size callers allocate).
-long long sum_groups(long long nchunk) { return nchunk > 64 ? (nchunk + 63) / 64 : 0; }
-
 // Fixed-order sum of nchunk partial rows ws[c * rs + i] (i < rs): entries
 // below nw go to dw, the rest to db.
 void enq_sum_rows(float* ws, long long nchunk, long long rs, long long nw, float* dw, float* db,
@@ -1163,19 +1160,20 @@ void enq_sum_rows(float* ws, long long nchunk, long long rs, long long nw, float
     hipLaunchKernelGGL(k_sum_rows<16>, grid, dim3(1024), 0, st, ws, rs, (int)nchunk, nw, dw, db);
 }
 
-// Partial rows and size class of the weight gradient, as
-// unet_wgrad_workspace and unet_wgrad_kernel report them.  Regular grids (rows:
+// Partial rows and size class of the weight gradient, as unet_wgrad_kernel
+// reports them.  Regular grids (rows:
 // w a multiple of 32 or 16, h of 4, 8 or a multiple of 16 input channels, 3x3x3
 // taps) split into 4-row blocks of 32-voxel rows (w a multiple of 32) or row
 // pairs (w = 16).  Channel parts start at 32 x 32 and are halved while the
 // grid would have fewer than 512 of them; d ranges of at least 4 planes
 // then bring it to about 1024, while the partial rows stay within 8 Mi floats.
-// All other grids split into chunks of voxels.  The kernels write at most as
-// many rows.
+// All other grids split into chunks of voxels.  The workspace holds these rows
+// (wgrad_rows: or a few more), the voxel-chunk kernel writes them and the tiled
+// kernel at most as many.
 struct WgradPlan {
   bool rows;
-  int ct, ot, ws, nws, nhb, nds, dper, ncp, nop;
-  long long nchunk, ngroup, rs, vchunk;
+  int ct, ot, ws, dper;
+  long long nchunk, rs, vchunk;
 };
 
 WgradPlan wgrad_plan(unet_shape s, int cin, int cout, int taps) {
@@ -1206,103 +1204,149 @@ WgradPlan wgrad_plan(unet_shape s, int cin, int cout, int taps) {
       p.ct = ct;
       p.ot = ot;
       p.ws = ws;
-      p.nws = s.w / ws;
-      p.nhb = s.h / 4;
-      p.ncp = cin / ct;
-      p.nop = cout / ot;
-      const long long base = cols * p.ncp * p.nop;
+      const long long base = cols * (cin / ct) * (cout / ot);
       const long long want = (1024 + base - 1) / base;
       int nds = (int)std::min<long long>(maxnds, std::max<long long>(1, want));
       // partial rows beyond 8 Mi floats cost more to sum than the split gains
       while (nds > 1 && cols * nds * p.rs > (8LL << 20)) nds = (nds + 1) / 2;
       p.dper = (s.d + nds - 1) / nds;
-      p.nds = (s.d + p.dper - 1) / p.dper;
-      p.nchunk = cols * p.nds;
+      p.nchunk = cols * ((s.d + p.dper - 1) / p.dper);
     }
   }
   if (!p.rows) {
     p.vchunk = wgrad_chunk(nv);
     p.nchunk = (nv + p.vchunk - 1) / p.vchunk;
   }
-  p.ngroup = sum_groups(p.nchunk);
   return p;
 }
 
 // Whether the tiled kernel (unet_wgrad.h) takes a weight gradient: 3x3x3 taps,
 // 8 or a multiple of 16 input channels, planes that a buffer descriptor spans
-// and voxels that an int counts.  Against the gathered voxel-chunk kernel, with
-// sums: 16 -> 16 channels on 48x56x104 37 and 211 us, 128 -> 128 on 2 x 12x20x28
-// 44 and 373, 64 -> 128 on 8x8x8 36 and 82; it is the faster one at every size.
+// and voxels that an int counts.
 bool wgrad_tiled(unet_shape s, int cin, int ld, int taps) {
   return taps == 27 && (cin == 8 || cin % 16 == 0) && (long long)s.h * s.w * ld < (1LL << 30) - 64 &&
          nvox_of(s) < (1LL << 31);
 }
 
-// Enqueues the tiled kernel; returns the number of partial rows (at most the
-// plan's).  Its workgroups fill every CU once (a CU holds PER_CU), split over
+// Partial rows that the workspace holds: the plan's, and up to 64 where they take
+// no more than 8 Mi floats, for grids whose voxels are few and whose tiles many
+// (the plan counts chunks of 1024 voxels).
+long long wgrad_rows(const WgradPlan& p) {
+  return std::max(p.nchunk, std::min(64LL, (8LL << 20) / p.rs));
+}
+
+// Estimated time (us) of the tiled kernel on shares of few planes (a step's latency
+// each, two short steps more at the start of a tile) and of writing and summing m
+// rows.
+double wgrad_us(unet_shape s, long long steps, int m, long long rs) {
+  const long long share = (steps + m - 1) / m;
+  return 7.5 + 2.0 * share + 1.4 * ((share + s.d - 1) / s.d) + m * (double)rs * 8 / 3e6;
+}
+
+// The tiled kernel's launch: instance, octets along w of a tile (2^ltwo), tiles
+// along w and h, channel parts and shares.
+struct WgradChoice {
+  int ct, ot, ltwo, nbw, nbh, nparts, nchunk;
+  long long steps;
+  double cost;
+  bool tiled;  // false: the voxel-chunk kernel is the faster one
+};
+
+// f(Wgrad<...>{}) of the instance for CT input and OT output channels
+template <typename F>
+auto with_wgrad(int ct, int ot, F&& f) {
+  if (ct == 8) return f(unet::Wgrad<8, 16, 2, 512>{});
+  if (ct == 16)
+    return ot == 16 ? f(unet::Wgrad<16, 16, 2, 512>{}) : f(unet::Wgrad<16, 32, 2, 512>{});
+  return ot == 16 ? f(unet::Wgrad<32, 16, 4, 256>{}) : f(unet::Wgrad<32, 32, 4, 256>{});
+}
+
+// Its workgroups fill every CU once (a CU holds PER_CU), split over
 // the channel parts; the tile is the one that pads the grid least, then the
-// one with the smallest halo.  Channel parts of 32 unless parts of 16 leave a
+// one with the smallest halo (64 wide only where that saves a third of the tiles:
+// grids of few rows; 48 -> 16 channels on 4 x 38x4x288 39 us, 56 at 32 wide).  More
+// shares than the plan's rows where that takes a fifth off the estimate: 32 -> 32
+// on 127x2x1 320 us with its one share, 16 with 64; 16 -> 16 on 1x1x4096 135 and 16.
+// Channel parts of 32 unless parts of 16 leave a
 // workgroup fewer steps, six counted for its start and end: the plan's rows
 // bound the workgroups of a part (32 -> 32 channels on 24x28x52: 35 rows,
 // parts of 32 31.5 us, of 16 18.2; 32 -> 16 on 2 x 128^3: 110 and 136).
-long long enq_wgrad(unet_shape s, unet_act x, unet_act dy, const WgradPlan& p, float* ws,
-                    hipStream_t st) {
-  using namespace unet;
-  WgradArgs a{s, (const uint16_t*)x.p, x.ld, x.off, x.c, (const uint16_t*)dy.p, dy.ld, dy.off, dy.c,
-              0, 0, 0, 0, 0, 0, p.rs, ws};
-  struct Choice {
-    int ltwo, nbw, nbh, nparts, nchunk;
-    long long steps;
-    double cost;
+WgradChoice wgrad_tiling(unet_shape s, int cin, int cout, const WgradPlan& p) {
+  auto plan = [&](int ct, int ot, bool flat) {
+    return with_wgrad(ct, ot, [&](auto kc) {
+      using K = decltype(kc);
+      WgradChoice c{};
+      c.ct = K::CT;
+      c.ot = K::OT;
+      long long tiles = -1, halo = 0;
+      for (int lg : {2, 1, 0, 3}) {
+        const int two = 1 << lg, rows = K::NOC / two * K::RL;
+        if (two < K::TWO_LO || two > (flat ? K::TWO_HI : 4)) continue;
+        const int nbw = (s.w + 8 * two - 1) / (8 * two), nbh = (s.h + rows - 1) / rows;
+        const long long nt = (long long)nbw * nbh * s.n, h = (rows + 2LL) * (8 * two + 2);
+        if (tiles >= 0 && (nt > tiles || (nt == tiles && h >= halo))) continue;
+        if (two == 8 && 3 * nt > 2 * tiles) continue;
+        tiles = nt;
+        halo = h;
+        c.ltwo = lg;
+        c.nbw = nbw;
+        c.nbh = nbh;
+      }
+      c.steps = tiles * s.d;
+      c.nparts = cin / K::CT * (cout / K::OT);
+      const long long fill = std::min(c.steps, std::max(1LL, 256LL * K::PER_CU / c.nparts));
+      c.nchunk = (int)std::min(p.nchunk, fill);
+      // more rows than the plan's where a share would walk long alone
+      const int most = (int)std::min({wgrad_rows(p), fill, std::max(1LL, 256LL / c.nparts)});
+      int best = c.nchunk;
+      for (int m = c.nchunk + 1; m <= most; ++m)
+        if (wgrad_us(s, c.steps, m, p.rs) < wgrad_us(s, c.steps, best, p.rs)) best = m;
+      if (wgrad_us(s, c.steps, best, p.rs) < 0.8 * wgrad_us(s, c.steps, c.nchunk, p.rs))
+        c.nchunk = best;
+      // a second workgroup on a CU takes half its time again (measured), more than
+      // the CUs hold run in turns
+      const double per_cu = (double)c.nchunk * c.nparts / 256;
+      const double turns = per_cu <= 1 ? 1 : (per_cu <= 2 ? 0.5 + 0.5 * per_cu : per_cu * 0.75);
+      c.cost = ((c.steps + c.nchunk - 1) / c.nchunk + 6) * turns;
+      return c;
+    });
   };
-  auto plan = [&](auto kc) {
-    using K = decltype(kc);
-    Choice c{};
-    long long tiles = -1, halo = 0;
-    for (int two = K::TWO_HI, lg = 2; two >= K::TWO_LO; two /= 2, --lg) {
-      const int rows = K::NOC / two * K::RL;
-      const int nbw = (s.w + 8 * two - 1) / (8 * two), nbh = (s.h + rows - 1) / rows;
-      const long long nt = (long long)nbw * nbh * s.n, h = (rows + 2LL) * (8 * two + 2);
-      if (tiles >= 0 && (nt > tiles || (nt == tiles && h >= halo))) continue;
-      tiles = nt;
-      halo = h;
-      c.ltwo = lg;
-      c.nbw = nbw;
-      c.nbh = nbh;
-    }
-    c.steps = tiles * s.d;
-    c.nparts = x.c / K::CT * (dy.c / K::OT);
-    c.nchunk = (int)std::min({p.nchunk, c.steps, std::max(1LL, 256LL * K::PER_CU / c.nparts)});
-    // a second workgroup on a CU takes half its time again (measured), more than
-    // the CUs hold run in turns
-    const double per_cu = (double)c.nchunk * c.nparts / 256;
-    const double turns = per_cu <= 1 ? 1 : (per_cu <= 2 ? 0.5 + 0.5 * per_cu : per_cu * 0.75);
-    c.cost = ((c.steps + c.nchunk - 1) / c.nchunk + 6) * turns;
+  if (cin == 8) return plan(8, 16, true);
+  if (cin % 32 && cout % 32) return plan(16, 16, true);
+  const WgradChoice base = plan(16, 16, false);
+  const WgradChoice wide = plan(cin % 32 ? 16 : 32, cout % 32 ? 16 : 32, true);
+  return wide.cost <= base.cost ? wide : base;
+}
+
+// Tiles or voxel chunks, by estimate: chunks (their bias sums walk up to 1024
+// voxels one after another, 85 us) are the faster ones on irregular grids of a few
+// voxels only: 128 -> 128 on 2x2x2 13.2 us and 14.0, on 1x1x4096 159 and 40; 16 ->
+// 16 on 48x56x104 211 and 37, 64 -> 128 on 8x8x8 82 and 36.
+WgradChoice wgrad_choice(unet_shape s, int cin, int cout, const WgradPlan& p) {
+  WgradChoice c = wgrad_tiling(s, cin, cout, p);
+  const int ob = cout / 16;
+  if (p.rows || !(ob == 1 || ob == 2 || ob == 4 || ob == 8)) {
+    c.tiled = true;
     return c;
-  };
-  auto go = [&](auto kc) -> long long {
+  }
+  const double nv = (double)nvox_of(s), vchunk = std::min(nv, (double)p.vchunk);
+  const double wgs = std::ceil(27 * cin / 64.0) * p.nchunk;
+  const double us = ob == 1 ? 12 : (ob == 2 ? 30 : (ob == 4 ? 43 : 50));
+  const double chunks = 11.5 + vchunk / 1024 * (85 + wgs / 256 * us) + p.nchunk * p.rs * 8 / 3e6;
+  c.tiled = wgrad_us(s, c.steps, c.nchunk, p.rs) <= chunks;
+  return c;
+}
+
+void enq_wgrad(unet_shape s, unet_act x, unet_act dy, const WgradChoice& c, long long rs, float* ws,
+               hipStream_t st) {
+  const WgradArgs a{s, (const uint16_t*)x.p, x.ld, x.off, x.c, (const uint16_t*)dy.p, dy.ld, dy.off,
+                    dy.c, c.ltwo, c.nbw, c.nbh, x.c / c.ct, (int)(c.steps / c.nchunk),
+                    (int)(c.steps % c.nchunk), rs, ws};
+  with_wgrad(c.ct, c.ot, [&](auto kc) {
     using K = decltype(kc);
-    const Choice c = plan(kc);
-    a.ltwo = c.ltwo;
-    a.nbw = c.nbw;
-    a.nbh = c.nbh;
-    a.ncp = x.c / K::CT;
-    a.q = (int)(c.steps / c.nchunk);
-    a.r = (int)(c.steps % c.nchunk);
-    hipLaunchKernelGGL((k_wgrad<K::CT, K::OT, K::RL, K::NT>), dim3(c.nchunk, c.nparts), dim3(K::NT),
-                       0, st, a);
-    return c.nchunk;
-  };
-  constexpr Wgrad<8, 16, 2, 512> k8{};
-  constexpr Wgrad<16, 16, 2, 512> k16{};
-  constexpr Wgrad<16, 32, 2, 512> k16w{};
-  constexpr Wgrad<32, 16, 4, 256> k32{};
-  constexpr Wgrad<32, 32, 4, 256> k32w{};
-  if (x.c == 8) return go(k8);
-  if (x.c % 32 == 0 && dy.c % 32 == 0 && plan(k32w).cost <= plan(k16).cost) return go(k32w);
-  if (x.c % 32 == 0 && dy.c % 32 && plan(k32).cost <= plan(k16).cost) return go(k32);
-  if (x.c % 32 && dy.c % 32 == 0 && plan(k16w).cost <= plan(k16).cost) return go(k16w);
-  return go(k16);
+    hipLaunchKernelGGL((unet::k_wgrad<K::CT, K::OT, K::RL, K::NT>), dim3(c.nchunk, c.nparts),
+                       dim3(K::NT), 0, st, a);
+  });
 }
 
 }  // namespace
@@ -1462,7 +1506,7 @@ unet_status unet_conv_dgrad_relu(unet_shape s, unet_act dy, const void* w, int32
 size_t unet_wgrad_workspace(unet_shape s, int32_t cin, int32_t cout, int32_t taps) {
   if (!shape_ok(s) || cin <= 0 || cout <= 0 || (taps != 27 && taps != 1)) return 0;
   const WgradPlan p = wgrad_plan(s, cin, cout, taps);
-  return (size_t)((p.nchunk + p.ngroup) * p.rs) * sizeof(float);
+  return (size_t)(wgrad_rows(p) * p.rs) * sizeof(float);
 }
 
 unet_status unet_wgrad_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t taps,
@@ -1477,6 +1521,21 @@ unet_status unet_wgrad_kernel(unet_shape s, int32_t cin, int32_t cout, int32_t t
   info[3] = p.ws;
   info[4] = (int32_t)p.nchunk;
   info[5] = p.dper;
+  return UNET_OK;
+}
+
+unet_status unet_wgrad_launch(unet_shape s, int32_t cin, int32_t xld, int32_t cout, int32_t dld,
+                              int32_t taps, int32_t* info) {
+  if (!info || !shape_ok(s) || cin <= 0 || cin % 8 || xld < cin || xld % 8 || cout <= 0 ||
+      cout % 16 || cout > 128 || dld < cout || dld % 8 || (taps != 27 && taps != 1))
+    return ufail(UNET_EINVAL, "bad wgrad_launch args");
+  const WgradPlan p = wgrad_plan(s, cin, cout, taps);
+  std::fill(info, info + 6, 0);
+  if (!wgrad_tiled(s, cin, std::max(xld, dld), taps)) return UNET_OK;
+  const WgradChoice c = wgrad_choice(s, cin, cout, p);
+  if (!c.tiled) return UNET_OK;
+  info[0] = 1, info[1] = c.ct, info[2] = c.ot, info[3] = 1 << c.ltwo, info[4] = c.nchunk,
+  info[5] = c.nparts;
   return UNET_OK;
 }
 
@@ -1496,8 +1555,11 @@ unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps,
   if (!p.rows && obs != 1 && obs != 2 && obs != 4 && obs != 8)
     return ufail(UNET_EINVAL, "output channels must be 16, 32, 64 or 128");
   long long nchunk = p.nchunk;
-  if (wgrad_tiled(s, x.c, std::max(x.ld, dy.ld), taps)) {
-    nchunk = enq_wgrad(s, x, dy, p, wsp, st);
+  WgradChoice c{};
+  if (wgrad_tiled(s, x.c, std::max(x.ld, dy.ld), taps)) c = wgrad_choice(s, x.c, dy.c, p);
+  if (c.tiled) {
+    nchunk = c.nchunk;
+    enq_wgrad(s, x, dy, c, p.rs, wsp, st);
   } else {
     const long long nv = nvox_of(s);
     const long long vchunk = p.rows ? ((nv + nchunk - 1) / nchunk + 31) / 32 * 32 : p.vchunk;
@@ -1645,7 +1707,7 @@ size_t unet_head_workspace(unet_shape s, int32_t cin) {
   const long long nv = nvox_of(s);
   const long long ch = wgrad_chunk(nv);
   const long long nc = (nv + ch - 1) / ch;
-  return (size_t)(nc + sum_groups(nc)) * (cin + 1) * sizeof(float);
+  return (size_t)nc * (cin + 1) * sizeof(float);
 }
 
 static unet_status head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,

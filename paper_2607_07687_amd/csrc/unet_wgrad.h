@@ -28,7 +28,8 @@ using LdsBytes = __attribute__((address_space(3))) char*;
 // Compile-time shape of a weight-gradient kernel: CT input and OT output
 // channels per workgroup, in P blocks of 16 x 16; a wave holds one block's 27
 // taps and takes four octets (8 voxels of a row) at a time, one per 16 lanes,
-// down a chain of RL rows.  A tile is NOC octets: two along w, thb chains along h.
+// down a chain of RL rows.  A tile is NOC octets: two of them along w (1 to 8), the
+// chains along h.
 //
 // The MFMA's K runs over voxels, so that a lane wants 8 voxels of one channel
 // where memory holds the channels of a voxel together: the tiles stay as they
@@ -66,8 +67,9 @@ struct Wgrad {
   }
   static constexpr int most(int a, int b) { return a > b ? a : b; }
   // octets along w of a tile (a power of two): the widest and narrowest
-  static constexpr int TWO_HI = 4, TWO_LO = NOC > 8 ? 2 : 1;
-  static constexpr int XS = most(most(xslots(4), xslots(2)), xslots(TWO_LO)) + (CT == 8 ? 1 : 0);
+  static constexpr int TWO_HI = NOC > 8 ? 8 : 4, TWO_LO = NOC > 8 ? 2 : 1;
+  static constexpr int XS =
+      most(most(xslots(TWO_HI), xslots(4)), most(xslots(2), xslots(TWO_LO))) + (CT == 8 ? 1 : 0);
   static constexpr int DS = NOC * 8 * RL;
   static constexpr int NIX = (XS * XQ + NT - 1) / NT, NID = DS * DQ / NT;
   static constexpr int XB = NIX * NT * 16, DB = DS * DQ * 16;  // bytes of one plane's buffer

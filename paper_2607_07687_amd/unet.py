@@ -43,6 +43,7 @@ _SIGS = [
     ("unet_wgrad_workspace", ctypes.c_size_t, [unet_shape, _I, _I, _I]),
     ("unet_conv_wgrad", ctypes.c_int, [unet_shape, unet_act, unet_act, _I, _V, _V, _V, _V]),
     ("unet_wgrad_kernel", ctypes.c_int, [unet_shape, _I, _I, _I, _V]),
+    ("unet_wgrad_launch", ctypes.c_int, [unet_shape, _I, _I, _I, _I, _I, _V]),
     ("unet_conv_launch", ctypes.c_int, [unet_shape, _I, _I, _I, _I, _V]),
     ("unet_conv_kernel", ctypes.c_int, [unet_shape, _I, _I, _I, _V]),
     ("unet_relu_bwd", ctypes.c_int, [unet_shape, unet_act, unet_act, unet_act, _V]),
@@ -166,6 +167,15 @@ def unet_conv_launch(s, cin, cout, taps, xld=None):
     if info[0] == 1:
         return ("brick",) + tuple(info[1:7])
     return ("gather", info[3], info[4])
+
+
+def unet_wgrad_launch(s, cin, cout, taps, xld=None, dld=None):
+    """The kernel unet_conv_wgrad launches (host only): ("tiled", input channels,
+    output channels, octets along w) or ("chunk",), and the tiled one's shares."""
+    info = (ctypes.c_int32 * 6)()
+    _check(load().unet_wgrad_launch(s, cin, xld or cin, cout, dld or cout, taps,
+                                    ctypes.cast(info, ctypes.c_void_p)))
+    return (("tiled",) + tuple(info[1:4]) if info[0] else ("chunk",)), info[4]
 
 
 def unet_wgrad_kernel(s, cin, cout, taps):

@@ -1,10 +1,12 @@
 """GPU parity of every instance of the convolution kernels that a size can
 choose (test_unet_dispatch.py checks on the host that the cases reach them all):
-forward in FP32 and BF16, and the gated data gradient where the channels allow
-one, on ragged grids, against FP64 sums over the valid pairs of voxels."""
+forward in FP32 and BF16, the gated data gradient where the channels allow one,
+and the weight gradient, on ragged grids, against FP64 sums over the valid pairs
+of voxels."""
 import pytest
 
 from paper_2607_07687_amd import unet as UN
+from tests import test_gpu_unet_wgrad as WG
 from tests.gpu_util import require_gpu, say, torch
 
 pytestmark = pytest.mark.gpu
@@ -25,6 +27,18 @@ CONV = [
     # gathered operands: grids one or two voxels wide
     (2, 229, 1, 1, 32, 128), (2, 149, 17, 1, 16, 128), (2, 26, 156, 1, 16, 128),
     (1, 163, 99, 1, 16, 128), (2, 223, 73, 1, 16, 128), (2, 43, 380, 2, 16, 128),
+]
+
+WGRAD = [
+    # (input, output channels, octets along w) of a workgroup's tile
+    (1, 8, 54, 43, 8, 16), (1, 5, 13, 29, 8, 16), (2, 5, 6, 70, 8, 32), (1, 5, 33, 15, 16, 16),
+    (1, 5, 14, 30, 16, 16), (1, 7, 5, 75, 48, 16), (1, 5, 15, 9, 16, 32), (2, 5, 7, 30, 16, 32),
+    (1, 5, 3, 70, 16, 64), (1, 20, 58, 6, 32, 16), (1, 6, 15, 14, 32, 16), (1, 6, 7, 30, 64, 16),
+    (1, 24, 28, 135, 64, 64), (1, 11, 22, 6, 128, 64), (1, 6, 7, 14, 32, 32), (1, 6, 3, 30, 32, 64),
+    # many tiles of few voxels
+    (2, 160, 1, 1, 96, 64), (1, 127, 2, 1, 32, 32), (1, 1, 1, 4096, 16, 16), (1, 117, 1, 1, 8, 32),
+    # voxel chunks
+    (1, 6, 1, 1, 48, 128), (1, 2, 2, 2, 16, 16),
 ]
 
 
@@ -84,3 +98,26 @@ def test_conv_instances(case):
                             fl)
     UN.unet_conv_fwd(s, xa, wt, None, 27, UN.act(None, cout, 0, cout), yf, 0)
     assert torch.equal(dx, torch.where(gate > 0, yf, 0.0).to(torch.bfloat16))
+
+
+@pytest.mark.parametrize("case", WGRAD, ids=lambda c: "x".join(map(str, c)))
+def test_wgrad_instances(case):
+    require_gpu()
+    n, d, h, w, cin, cout = case
+    s = UN.shape(n, d, h, w)
+    say(f"wgrad {case} {UN.unet_wgrad_launch(s, cin, cout, 27, cin + 16)}")
+    g = torch.Generator(device="cuda").manual_seed(sum(case))
+    x = torch.randn(n, d, h, w, cin, device="cuda", generator=g).to(torch.bfloat16)
+    dy = torch.randn(n, d, h, w, cout, device="cuda", generator=g).to(torch.bfloat16)
+    dw, db = WG.run(s, x, dy, cin + 16, 8)
+    rw, rb = WG.reference(x.double(), dy.double())
+    mw, mb = WG.reference(x.double(), dy.double(), magnitude=True)
+    tol = 256 * 2.0 ** -24  # of the sums of magnitudes, as in test_gpu_unet_wgrad.py
+    assert ((dw.double() - rw).abs() <= tol * mw).all()
+    assert ((db.double() - rb).abs() <= tol * mb).all()
+    # infinities at two corners reach only the taps that pair them with a voxel
+    x[0, d - 1, h - 1, w - 1, 0] = float("inf")
+    x[0, 0, 0, 0, cin - 1] = float("inf")
+    dw, db = WG.run(s, x, dy, cin + 16, 8)
+    rw, _ = WG.reference(x.double(), dy.double())
+    assert torch.equal(dw.isfinite(), rw.isfinite()) and db.isfinite().all()

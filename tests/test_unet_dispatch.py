@@ -1,12 +1,12 @@
-"""Host-side choice of the convolution kernels, from unet_conv_launch (no GPU
-call): grids that waste a brick or a marching tile take another kernel, those
-that fill them do not."""
+"""Host-side choice of the convolution and weight-gradient kernels, from
+unet_conv_launch and unet_wgrad_launch (no GPU call): grids that waste a brick, a
+tile or a share take another one, those that fill them do not."""
 import random
 
 import pytest
 
 from paper_2607_07687_amd import unet as UN
-from tests.test_gpu_unet_dispatch import CONV
+from tests.test_gpu_unet_dispatch import CONV, WGRAD
 
 
 def conv(n, d, h, w, cin, cout):
@@ -89,3 +89,48 @@ def test_cases_cover_every_convolution_instance():
                 assert k in seen, (k, g, cin, cout)
     assert len([k for k in seen if k[0] == "brick"]) == 21
     assert len([k for k in seen if k[0] == "march"]) == 4
+
+
+def wgrad(n, d, h, w, cin, cout):
+    return UN.unet_wgrad_launch(UN.shape(n, d, h, w), cin, cout, 27)
+
+
+@pytest.mark.parametrize("case,least", [
+    ((1, 127, 2, 1, 32, 32), 32), ((1, 117, 1, 1, 8, 32), 32), ((1, 1, 1, 4096, 16, 16), 64),
+    ((4, 1, 112, 1, 64, 16), 12)])
+def test_grids_of_few_voxels_have_shares(case, least):
+    # not one share, or one per 1024 voxels, that walks alone; what it writes
+    # fits the workspace
+    kernel, shares = wgrad(*case)
+    cin, cout = case[4:]
+    assert kernel[0] == "tiled" and shares >= least
+    assert shares * (cout * 27 * cin + cout) * 4 <= UN.unet_wgrad_workspace(
+        UN.shape(*case[:4]), cin, cout, 27)
+
+
+def test_a_few_voxels_go_in_chunks():
+    assert wgrad(1, 2, 2, 2, 16, 16)[0] == ("chunk",)
+    assert wgrad(1, 2, 2, 2, 256, 128)[0] == ("chunk",)
+    # or many, of which a tile would hold four a plane
+    assert wgrad(1, 16384, 2, 2, 16, 16)[0] == ("chunk",)
+    assert wgrad(1, 8, 8, 8, 64, 128)[0] == ("tiled", 32, 32, 2)
+
+
+def test_cases_cover_every_weight_gradient_instance():
+    seen = {wgrad(*c)[0] for c in WGRAD}
+    for g in sizes(2, 4000):
+        for cin in (8, 16, 32, 48, 64, 128):
+            for cout in (16, 32, 64, 128):
+                k, shares = wgrad(*g, cin, cout)
+                assert k in seen, (k, g, cin, cout)
+                assert shares * (cout * 27 * cin + cout) * 4 <= UN.unet_wgrad_workspace(
+                    UN.shape(*g), cin, cout, 27)
+    assert len(seen) == 16
+
+
+def test_bad_wgrad_arguments():
+    s = UN.shape(1, 8, 8, 8)
+    for args in ((s, 12, 16, 27), (s, 16, 40, 27), (s, 16, 144, 27), (s, 16, 16, 9),
+                 (s, 16, 16, 27, 8), (s, 16, 16, 27, 16, 12), (UN.shape(1, 8, 0, 8), 16, 16, 27)):
+        with pytest.raises(UN.UNetError):
+            UN.unet_wgrad_launch(*args)
