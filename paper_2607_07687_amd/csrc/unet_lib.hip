@@ -1221,11 +1221,11 @@ WgradPlan wgrad_plan(unet_shape s, int cin, int cout, int taps) {
 }
 
 // Whether the tiled kernel (unet_wgrad.h) takes a weight gradient: 3x3x3 taps,
-// 8 or a multiple of 16 input channels, planes that a buffer descriptor spans
-// and voxels that an int counts.
+// 8 or a multiple of 16 input channels, voxels that an int counts and rows of a
+// tile (34 at most) that a buffer descriptor spans.
 bool wgrad_tiled(unet_shape s, int cin, int ld, int taps) {
-  return taps == 27 && (cin == 8 || cin % 16 == 0) && (long long)s.h * s.w * ld < (1LL << 30) - 64 &&
-         nvox_of(s) < (1LL << 31);
+  return taps == 27 && (cin == 8 || cin % 16 == 0) && nvox_of(s) < (1LL << 31) &&
+         offsets_fit(0, 36, s, ld);
 }
 
 // Partial rows that the workspace holds: the plan's, and up to 64 where they take
@@ -1344,8 +1344,13 @@ void enq_wgrad(unet_shape s, unet_act x, unet_act dy, const WgradChoice& c, long
                     (int)(c.steps % c.nchunk), rs, ws};
   with_wgrad(c.ct, c.ot, [&](auto kc) {
     using K = decltype(kc);
-    hipLaunchKernelGGL((unet::k_wgrad<K::CT, K::OT, K::RL, K::NT>), dim3(c.nchunk, c.nparts),
-                       dim3(K::NT), 0, st, a);
+    const dim3 grid(c.nchunk, c.nparts);
+    if (offsets_fit(1, 0, s, std::max(x.ld, dy.ld)))
+      hipLaunchKernelGGL((unet::k_wgrad<K::CT, K::OT, K::RL, K::NT, false>), grid, dim3(K::NT), 0,
+                         st, a);
+    else
+      hipLaunchKernelGGL((unet::k_wgrad<K::CT, K::OT, K::RL, K::NT, true>), grid, dim3(K::NT), 0,
+                         st, a);
   });
 }
 
@@ -1565,19 +1570,17 @@ unet_status unet_conv_wgrad(unet_shape s, unet_act x, unet_act dy, int32_t taps,
     const long long vchunk = p.rows ? ((nv + nchunk - 1) / nchunk + 31) / 32 * 32 : p.vchunk;
     nchunk = (nv + vchunk - 1) / vchunk;
     const dim3 grid((K + 63) / 64, (unsigned)nchunk);
-    auto launch = [&](auto ob) {
+    auto launch = [&](auto ob, int o) {  // output channels from block o on
       hipLaunchKernelGGL(k_conv_wgrad<decltype(ob)::value>, grid, dim3(256), 0, st, s, xp, x.ld,
-                         x.off, x.c, dp, dy.ld, dy.off, taps, vchunk, p.rs, wsp);
+                         x.off, x.c, dp, dy.ld, dy.off + 16 * o, taps, vchunk, p.rs,
+                         wsp + 16LL * o * K);
     };
     switch (obs) {
-      case 1: launch(std::integral_constant<int, 1>{}); break;
-      case 2: launch(std::integral_constant<int, 2>{}); break;
-      case 3: launch(std::integral_constant<int, 3>{}); break;
-      case 4: launch(std::integral_constant<int, 4>{}); break;
-      case 5: launch(std::integral_constant<int, 5>{}); break;
-      case 6: launch(std::integral_constant<int, 6>{}); break;
-      case 7: launch(std::integral_constant<int, 7>{}); break;
-      default: launch(std::integral_constant<int, 8>{}); break;
+      case 2: launch(std::integral_constant<int, 2>{}, 0); break;
+      case 4: launch(std::integral_constant<int, 4>{}, 0); break;
+      case 8: launch(std::integral_constant<int, 8>{}, 0); break;
+      default:  // (of 3, 5, 6 and 7 blocks: regular grids past the tiled kernel's reach)
+        for (int o = 0; o < obs; ++o) launch(std::integral_constant<int, 1>{}, o);
     }
     hipLaunchKernelGGL(k_bias_partial, dim3((unsigned)nchunk), dim3(128), 0, st, s, dp, dy.ld,
                        dy.off, dy.c, vchunk, p.rs, wsp + nw);

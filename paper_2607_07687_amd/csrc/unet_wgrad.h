@@ -83,7 +83,9 @@ struct Wgrad {
 // above it, fetched while step k - 1 computes; dy planes stay for two more
 // steps.  The shares' sums go to ws, one row per share; k_sum_* add the rows
 // in order.
-template <int CT, int OT, int RL, int NT>
+// FAR: planes of 2^31 bytes and more, whose offsets count from the tile's first
+// rows.
+template <int CT, int OT, int RL, int NT, bool FAR>
 __global__ __launch_bounds__(NT, 2) void k_wgrad(WgradArgs a) {
   using K = Wgrad<CT, OT, RL, NT>;
   constexpr int XQ = K::XQ, DQ = K::DQ, NF = K::NF, P = K::P, KW = K::KW;
@@ -154,7 +156,7 @@ __global__ __launch_bounds__(NT, 2) void k_wgrad(WgradArgs a) {
       const int col = CT == 16 ? slot16(sl) : sl, q = CT == 32 ? q0 ^ swz32(col) : q0;
       const int h = s.h0 - 1 + row, w = s.w0 - 1 + col;
       xo[i] = row < rows + 2 && col < TW + 2 && (unsigned)h < (unsigned)H && (unsigned)w < (unsigned)W
-                  ? ((h * W + w) * a.xld + q * 8) * 2
+                  ? (((FAR ? row : h) * W + w) * a.xld + q * 8) * 2
                   : kOut;
     }
 #pragma unroll
@@ -162,17 +164,19 @@ __global__ __launch_bounds__(NT, 2) void k_wgrad(WgradArgs a) {
       const int e = tid + i * NT, q0 = e % DQ, v = e / DQ, row = v >> (a.ltwo + 3), sl = v & (TW - 1);
       const int col = OT == 16 ? slot16(sl) : sl, q = OT == 32 ? q0 ^ swz32(col) : q0;
       const int h = s.h0 + row, w = s.w0 + col;
-      dof[i] = row < rows && h < H && w < W ? ((h * W + w) * a.dld + q * 8) * 2 : kOut;
+      dof[i] = row < rows && h < H && w < W ? (((FAR ? row : h) * W + w) * a.dld + q * 8) * 2
+                                            : kOut;
     }
     return s;
   };
   const long long plane = (long long)H * W;
   auto fetch = [&](const Step& s) {
+    const long long xb = FAR ? (s.h0 - 1LL) * W : 0, db = FAR ? (long long)s.h0 * W : 0;
     const __amdgpu_buffer_rsrc_t xr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.x + ((long long)s.n * D + s.p) * plane * a.xld + a.xoff + c0), 0,
+        (void*)(a.x + (((long long)s.n * D + s.p) * plane + xb) * a.xld + a.xoff + c0), 0,
         (unsigned)s.p < (unsigned)D ? kOut : 0, 0x00020000);
     const __amdgpu_buffer_rsrc_t dr = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(a.dy + ((long long)s.n * D + s.p + 1) * plane * a.dld + a.doff + o0), 0,
+        (void*)(a.dy + (((long long)s.n * D + s.p + 1) * plane + db) * a.dld + a.doff + o0), 0,
         s.p < s.dl ? kOut : 0, 0x00020000);
 #pragma unroll
     for (int i = 0; i < K::NIX; ++i)
@@ -198,7 +202,7 @@ __global__ __launch_bounds__(NT, 2) void k_wgrad(WgradArgs a) {
     return __builtin_bit_cast(bf16x8, __builtin_shufflevector(u, v, 0, 1, 2, 3, 4, 5, 6, 7));
   };
 
-    constexpr uint32_t one2 = 0x3F803F80u;
+  constexpr uint32_t one2 = 0x3F803F80u;
   const bf16x8 ones = __builtin_bit_cast(bf16x8, make_uint4(one2, one2, one2, one2));
   // every wave sums the bias (those of the first input block store it): an MFMA
   // more for 27, but no branch among the taps

@@ -121,3 +121,22 @@ def test_wgrad_instances(case):
     dw, db = WG.run(s, x, dy, cin + 16, 8)
     rw, _ = WG.reference(x.double(), dy.double())
     assert torch.equal(dw.isfinite(), rw.isfinite()) and db.isfinite().all()
+
+
+@pytest.mark.parametrize("cout", [48, 80, 96])
+def test_odd_output_blocks_in_voxel_chunks(cout):
+    # regular grids take any multiple of 16 output channels, also where the rows of
+    # a tile are past a descriptor's reach
+    require_gpu()
+    n, d, h, w, cin, ld = 1, 1, 4, 4096, 16, 8192
+    s = UN.shape(n, d, h, w)
+    assert UN.unet_wgrad_launch(s, cin, cout, 27, ld)[0] == ("chunk",)
+    g = torch.Generator(device="cuda").manual_seed(cout)
+    x = torch.randn(n, d, h, w, cin, device="cuda", generator=g).to(torch.bfloat16)
+    dy = torch.randn(n, d, h, w, cout, device="cuda", generator=g).to(torch.bfloat16)
+    dw, db = WG.run(s, x, dy, ld, 8)
+    rw, rb = WG.reference(x.double(), dy.double())
+    mw, mb = WG.reference(x.double(), dy.double(), magnitude=True)
+    tol = 256 * 2.0 ** -24
+    assert ((dw.double() - rw).abs() <= tol * mw).all()
+    assert ((db.double() - rb).abs() <= tol * mb).all()

@@ -108,6 +108,13 @@ def test_grids_of_few_voxels_have_shares(case, least):
         UN.shape(*case[:4]), cin, cout, 27)
 
 
+def test_large_planes_are_tiled():
+    # planes of 2^30 elements; not the rows of a tile that span 2^31 bytes
+    assert wgrad(1, 2, 8192, 8192, 16, 16)[0][0] == "tiled"
+    assert wgrad(1, 1, 4096, 8192, 32, 32)[0][0] == "tiled"
+    assert wgrad(1, 1, 4, 1 << 22, 16, 16)[0] == ("chunk",)
+
+
 def test_a_few_voxels_go_in_chunks():
     assert wgrad(1, 2, 2, 2, 16, 16)[0] == ("chunk",)
     assert wgrad(1, 2, 2, 2, 256, 128)[0] == ("chunk",)
