@@ -45,13 +45,15 @@ template <typename T, typename TL, int VEC, bool PROL, int BZ>
 __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     Geom g, Roles<T> X, int rs, int rd, const T* __restrict__ sigma, const TL* __restrict__ L,
     const T* __restrict__ xc, const uint8_t* __restrict__ active, Geom gc, int cx, int cy, int cz,
-    const double* omega_p, const int* done) {
+    const double* omega_p, const int* done, int spare) {
   constexpr int RZ = BZ + 2 * CU_H, CU_Z = RZ / CU_G;  // region planes, planes per thread
   static_assert(RZ % CU_G == 0, "planes divide among the groups");
-  // first of all: behind the loads, whose latency it would share, the finished
-  // slots of a recorded solve load every cube (a slot of a 256 x 64 x 64
-  // refinement step took 42 us, now 25; live cycles take the same)
-  if (stopped(done)) return;
+  // `spare` launches, those of a refinement step's recorded cycles, most of which
+  // may find its solve finished: a finished slot of 256 x 64 x 64 took 42 us with
+  // the test behind the loads, 25 so.  Behind the loads (below) it shares their
+  // latency, which a solve's few slots beyond its end do not outweigh: solve 32^3
+  // FP64 641 us so, 649 with the test here.
+  if (spare && stopped(done)) return;
   __shared__ CubeSmem<T, RZ> sm;
   const T* __restrict__ S = X.get(rs);
   T* const W = X.get(rd);
@@ -146,6 +148,7 @@ __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     lz[CU_Z][1] = kw >= 0 && in1 ? lz[CU_Z][1] : T(0);
   }
   const T omega = (T)(*omega_p);
+  if (stopped(done)) return;
 #pragma unroll
   for (int z = 0; z < CU_Z; ++z) {
     sm.x[z0 + z][r][2 * p] = s[z][0];

@@ -961,6 +961,7 @@ struct gmg_handle {
   double* r64;       // FP64 outer residual
   float* b32;        // scaled, rounded correction right-hand side
   float* e32;        // correction (role 0 of the inner solve)
+  bool spare;        // the cycles being enqueued may well find their solve finished
   // captured launch sequences, replayed with hipGraphLaunch
   hipStream_t cap;   // capture stream (the caller's may be the legacy stream)
   CapturedSeq cyc;   // one V-cycle of gmg_solve
@@ -1196,7 +1197,8 @@ static void launch_cube(gmg_handle* h, int l, const Roles<T>& X, int rs, int rd,
     constexpr int BZ = decltype(bz)::value;
     hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value, BZ>),
                        dim3(nxy * ((lv.g.nz + BZ - 1) / BZ)), dim3(CU_NT), 0, h->s, lv.g, X, rs, rd,
-                       sigma, (const TL*)lv.L, xc, lv.active, gc, cx, cy, cz, &h->st->omega, done);
+                       sigma, (const TL*)lv.L, xc, lv.active, gc, cx, cy, cz, &h->st->omega, done,
+                       h->spare ? 1 : 0);
   };
   // half cubes while one per CU holds them all
   const bool halves = nxy * ((lv.g.nz + 3) / 4) <= 256;
@@ -1976,12 +1978,14 @@ static gmg_status ir_outer_step(gmg_handle* h, double* x, const double* sigma, i
                      h->partials + h->maxpart, np, h->st, inner_rtol, max_inner, h->p.omega0,
                      &h->ir->done, (const double*)&h->ir->inner_rtol);
   const Roles<float> XS{{h->e32, (float*)h->w[0], (float*)h->w[1]}, &h->st->cur};
+  h->spare = true;
   for (int c = 0; c < max_inner; ++c) {
     const int f = enq_vcycle<float, TL>(h, h->e32, &h->st->cur, h->b32, &h->st->done);
     enq_resnorm<float, TL>(h, XS, f, h->b32, (const TL*)lv.L, nullptr, 0, &h->st->done);
     hipLaunchKernelGGL(k_cycle_finish, dim3(1), dim3(256), 0, h->s, h->partials, np, h->st,
                        h->rule, f);
   }
+  h->spare = false;
   hipLaunchKernelGGL(k_ir_update, cell_grid(lv.g), kBlock, 0, h->s, lv.g, x, XS, h->ir,
                      (const SolveState*)h->st);
   HIP_TRY(hipGetLastError());
