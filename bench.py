@@ -509,7 +509,8 @@ def main():
     # warm-up, then K timed cycles of the adaptive solve
     tiles = AT.tune(h, x, sd, cache=None)  # timed sweep tiles per level (setup, untimed)
     log("tiles " + ", ".join(f"L{t['level']}:{t['ty']}x{t['kchunk']}" +
-                             (f"+pass{t.get('pair_ty', 16)}x{t['pair_kchunk']}"
+                             ("+cubes" if t.get("cube") else
+                              f"+pass{t.get('pair_ty', 16)}x{t['pair_kchunk']}"
                               if t.get("pair_kchunk") else "")
                              for t in tiles))
     x.zero_()

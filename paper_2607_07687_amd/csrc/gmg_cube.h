@@ -41,19 +41,20 @@ struct CubeSmem {
 // leave CUs idle, since the half-sweeps' arithmetic is most of a launch (FP64
 // above all, which divides): a launch on 32^3 FP64 takes 8.7 us with halves, 10
 // with whole cubes, on 30x22x18 FP32 7-9 and 8-10.
-template <typename T, typename TL, int VEC, bool PROL, int BZ>
+// SPARE: the cycles recorded for a refinement step, of which most may find its
+// solve finished: a finished slot of 256 x 64 x 64 takes 42 us with the test of the
+// flag behind the loads, 25 with it in front.  Behind them it shares their latency,
+// which a solve's few slots beyond its end do not outweigh (solve 32^3 FP64 641 us
+// so, 649 in front; a run-time choice costs a launch 0.3 us).
+template <typename T, typename TL, int VEC, bool PROL, int BZ, bool SPARE>
 __global__ __launch_bounds__(CU_NT) void k_rb_cube(
     Geom g, Roles<T> X, int rs, int rd, const T* __restrict__ sigma, const TL* __restrict__ L,
     const T* __restrict__ xc, const uint8_t* __restrict__ active, Geom gc, int cx, int cy, int cz,
-    const double* omega_p, const int* done, int spare) {
+    const double* omega_p, const int* done) {
   constexpr int RZ = BZ + 2 * CU_H, CU_Z = RZ / CU_G;  // region planes, planes per thread
   static_assert(RZ % CU_G == 0, "planes divide among the groups");
-  // `spare` launches, those of a refinement step's recorded cycles, most of which
-  // may find its solve finished: a finished slot of 256 x 64 x 64 took 42 us with
-  // the test behind the loads, 25 so.  Behind the loads (below) it shares their
-  // latency, which a solve's few slots beyond its end do not outweigh: solve 32^3
-  // FP64 641 us so, 649 with the test here.
-  if (spare && stopped(done)) return;
+  if constexpr (SPARE)
+    if (stopped(done)) return;
   __shared__ CubeSmem<T, RZ> sm;
   const T* __restrict__ S = X.get(rs);
   T* const W = X.get(rd);

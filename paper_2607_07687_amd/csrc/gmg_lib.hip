@@ -1193,12 +1193,20 @@ static void launch_cube(gmg_handle* h, int l, const Roles<T>& X, int rs, int rd,
   const Geom gc = (xc && l + 1 < h->nlev) ? h->lev[l + 1].g : lv.g;
   const int cx = lv.c[0] ? lv.c[0] : 1, cy = lv.c[1] ? lv.c[1] : 1, cz = lv.c[2] ? lv.c[2] : 1;
   const int nxy = ((lv.g.nx + CU_B - 1) / CU_B) * ((lv.g.ny + CU_B - 1) / CU_B);
-  auto go_z = [&](auto vec, auto prol, auto bz) {
+  auto go_spare = [&](auto vec, auto prol, auto bz, auto spare) {
     constexpr int BZ = decltype(bz)::value;
-    hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value, BZ>),
+    hipLaunchKernelGGL((k_rb_cube<T, TL, decltype(vec)::value, decltype(prol)::value, BZ,
+                                  decltype(spare)::value>),
                        dim3(nxy * ((lv.g.nz + BZ - 1) / BZ)), dim3(CU_NT), 0, h->s, lv.g, X, rs, rd,
-                       sigma, (const TL*)lv.L, xc, lv.active, gc, cx, cy, cz, &h->st->omega, done,
-                       h->spare ? 1 : 0);
+                       sigma, (const TL*)lv.L, xc, lv.active, gc, cx, cy, cz, &h->st->omega, done);
+  };
+  auto go_z = [&](auto vec, auto prol, auto bz) {
+    if constexpr (std::is_same<T, float>::value)  // refinement's cycles are FP32
+      if (h->spare) {
+        go_spare(vec, prol, bz, std::true_type{});
+        return;
+      }
+    go_spare(vec, prol, bz, std::false_type{});
   };
   // half cubes while one per CU holds them all
   const bool halves = nxy * ((lv.g.nz + 3) / 4) <= 256;
