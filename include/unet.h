@@ -138,7 +138,8 @@ unet_status unet_pool_bwd(unet_shape fine, unet_act dy, unet_act dx, int32_t acc
 unet_status unet_up_fwd(unet_shape coarse, unet_act x, unet_act y, void* stream);
 unet_status unet_up_bwd(unet_shape coarse, unet_act dy, unet_act dx, void* stream);
 /* The same with the ReLU backward of dx's layer (forward output y) in the same
- * pass, bitwise as the backward op followed by unet_relu_bwd on dx. */
+ * pass, bitwise as the backward op followed by unet_relu_bwd on dx.  y must not
+ * overlap dx. */
 unet_status unet_pool_bwd_relu(unet_shape fine, unet_act dy, unet_act y, unet_act dx,
                                int32_t accumulate, void* stream);
 unet_status unet_up_bwd_relu(unet_shape coarse, unet_act dy, unet_act y, unet_act dx, void* stream);
@@ -151,7 +152,8 @@ unet_status unet_head_fwd(unet_shape s, unet_act x, const float* w, const float*
 size_t unet_head_workspace(unet_shape s, int32_t cin);
 unet_status unet_head_bwd(unet_shape s, unet_act x, const float* w, const float* dy, unet_act dx,
                           float* dw, float* db, void* ws, void* stream);
-/* The same with dx cleared where x is not positive (x is a ReLU's output). */
+/* The same with dx cleared where x is not positive (x is a ReLU's output, not
+ * overlapping dx). */
 unet_status unet_head_bwd_relu(unet_shape s, unet_act x, const float* w, const float* dy,
                                unet_act dx, float* dw, float* db, void* ws, void* stream);
 

@@ -963,7 +963,9 @@ BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
       const double t = std::ceil(items / 256.0) * kBrickUs[nb - 1][sh][brick_class(ck, nc)];
       if (items < 2e9 && (best.shape < 0 || t < tbest)) {
         tbest = t;
-        best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd, 3 + t * (nc == 1 ? cin / ck : 1)};
+        // (passes after the first overlap)
+        best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd,
+                         3 + (nc == 1 && cin > ck ? 0.85 * cin / ck * t : t)};
       }
     }
   }
@@ -1047,7 +1049,7 @@ struct MarchPlan {
 // grid).  Against bricks, us (in brackets the estimates): 8 -> 16 on 2 x 128^3 49 /
 // 61 (48 / 70), on 48x56x104 11.1 / 10.7; 16 -> 16 on 2 x 128^3 72 / 91 (72 / 93),
 // 100x90x120 27.7 / 28.7, 48x56x104 15.5 / 11.5; 16 -> 32 on 2 x 128^3 135 / 166 (136
-// / 157), 2 x 64^3 22.8 / 22.7; 32 -> 16 on 2 x 128^3 131 / 158 (131 / 153),
+// / 157), 2 x 64^3 22.8 / 22.7; 32 -> 16 on 2 x 128^3 131 / 158 (126 / 153),
 // 100x90x120 42.8 / 43.7, 64^3 15.4 / 11.9; 32 -> 32 on 2 x 64^3 37.5 / 36.4, 32 ->
 // 64 64.5 / 68.3.  Flat grids, where a brick's other planes lie outside: 16 -> 16
 // on 512 x 512 9.9 / 15.3, 16 -> 32 on 8 x 256 x 256 22 / 43.  Narrow ones, where
@@ -1067,8 +1069,8 @@ MarchPlan march_plan(unet_shape s, int cin, int xld, int cout) {
     p.groups = cout / 16 / K::NB;
     p.nchunk = std::min(p.steps, std::max(1LL, 256LL * K::PER_CU / p.groups));
     const double used = (double)s.w * s.h / ((double)p.nbw * tw * p.nbh * th);
-    const double us = cin == 8 ? (p.groups > 1 ? 3.3 : 2.6) : (cin == 16 ? 4.0 : 3.85);
-    p.us = 4 + (std::ceil((double)p.steps / p.nchunk) + 1) * us * (0.7 + 0.3 * used);
+    const double us = cin == 8 ? (p.groups > 1 ? 3.3 : 2.6) : (cin == 16 ? 4.0 : 3.7);
+    p.us = 4 + (std::ceil((double)p.steps / p.nchunk) + 1) * us * (0.8 + 0.2 * used);
     return true;
   });
   return p;
