@@ -933,7 +933,8 @@ constexpr bool brick_exists(int shape, int ck, int nc, int nb) {
 struct BrickPlan {
   int ck, nc, shape, nb;  // shape < 0: no brick kernel for these sizes
   int nbw, nbh, nbd;
-  double us;  // estimated time
+  double us;        // estimated time
+  double us_march;  // the same as compared with the marching kernel's
 };
 
 // Whether the byte offsets of `planes` whole planes and `rows` rows of xld channels
@@ -945,7 +946,9 @@ bool offsets_fit(int planes, int rows, unet_shape s, int xld) {
 // The instance with the least estimated time (work items in rounds of 256 CUs,
 // times kBrickUs): the fastest one on the grids measured, or within 8 % of it.
 // Every instance gives bitwise the same result (8 to 128 channels in powers of
-// two: all products in (tap, channel) order).
+// two: all products in (tap, channel) order).  us_march is fitted to grids that
+// either of the two kernels might take: there the last-level cache holds the
+// operands, and a tall brick takes less than kBrickUs, measured on 2 x 128^3.
 BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
   BrickPlan best{};
   best.shape = -1;
@@ -965,7 +968,10 @@ BrickPlan brick_plan(unet_shape s, int cin, int xld, int cout) {
         tbest = t;
         // (passes after the first overlap)
         best = BrickPlan{ck, nc, sh, nb, nbw, nbh, nbd,
-                         3 + (nc == 1 && cin > ck ? 0.85 * cin / ck * t : t)};
+                         3 + (nc == 1 && cin > ck ? 0.85 * cin / ck * t : t), 0};
+        const double cached = b.mb == 4 ? 1.0 : (b.wc == 4 ? 0.9 : (b.wc == 2 ? 0.87 : 0.85));
+        const double used = (double)s.w * s.h * s.d / (16.0 * nbw * b.mb * nbh * b.wd * nbd);
+        best.us_march = 4 + t * cached * (0.8 + 0.2 * used);
       }
     }
   }
@@ -1045,16 +1051,19 @@ struct MarchPlan {
 };
 
 // The marching kernel's launch and estimated time: one step more than a
-// workgroup's share, of 2.6 to 4 us each (less where the tile reaches past the
-// grid).  Against bricks, us (in brackets the estimates): 8 -> 16 on 2 x 128^3 49 /
-// 61 (48 / 70), on 48x56x104 11.1 / 10.7; 16 -> 16 on 2 x 128^3 72 / 91 (72 / 93),
-// 100x90x120 27.7 / 28.7, 48x56x104 15.5 / 11.5; 16 -> 32 on 2 x 128^3 135 / 166 (136
-// / 157), 2 x 64^3 22.8 / 22.7; 32 -> 16 on 2 x 128^3 131 / 158 (126 / 153),
-// 100x90x120 42.8 / 43.7, 64^3 15.4 / 11.9; 32 -> 32 on 2 x 64^3 37.5 / 36.4, 32 ->
-// 64 64.5 / 68.3.  Flat grids, where a brick's other planes lie outside: 16 -> 16
-// on 512 x 512 9.9 / 15.3, 16 -> 32 on 8 x 256 x 256 22 / 43.  Narrow ones, where
-// most of a tile does: 32 -> 32 on 4096 x 8 x 8 84 / 29, 16 -> 16 on 4096 x 16 x 16
-// 34 / 24.
+// workgroup's share, of 2.7 to 3.8 us each (less where the tile reaches past the
+// grid).  The line between this kernel and the bricks follows from 200 ragged and
+// regular grids timed with both, us (in brackets the estimates): 16 -> 16 on
+// 100x90x120 27.7 / 28.7 (27.2 / 27.2), 48x56x104 15.5 / 11.5 (15.7 / 11.0); 16 -> 32
+// on 2 x 64^3 22.8 / 22.7 (22.0 / 20.3), 109x127x135 57.4 / 64.5 (67.5 / 68.0); 32 ->
+// 16 on 124x75x49 26.5 / 21.3 (24.8 / 22.8), 100x90x120 42.8 / 43.7 (42.6 / 43.0);
+// 32 -> 64 on 2 x 64^3 64.5 / 68.3 (64.5 / 65.9), 83x120x13 42.8 / 23.4.  The kernel
+// chosen was within 9 % of the faster one, 0.2 % in the mean (on 220 others 14 %,
+// 2 us).  Beyond the cache both take longer: 2 x 128^3 8 -> 16 49 / 61 (51 / 61), 16
+// -> 16 72 / 91 (70 / 80), 16 -> 32 135 / 166 (117 / 135), 32 -> 16 131 / 158 (121 /
+// 132).  Flat grids, where a brick's other planes lie outside: 16 -> 16 on 512 x 512
+// 9.9 / 15.3, 16 -> 32 on 8 x 256 x 256 22 / 43.  Narrow ones, where most of a tile
+// does: 32 -> 32 on 4096 x 8 x 8 84 / 29, 16 -> 16 on 4096 x 16 x 16 34 / 24.
 MarchPlan march_plan(unet_shape s, int cin, int xld, int cout) {
   MarchPlan p{};
   with_march(cin, cout, [&](auto kc) {
@@ -1069,8 +1078,9 @@ MarchPlan march_plan(unet_shape s, int cin, int xld, int cout) {
     p.groups = cout / 16 / K::NB;
     p.nchunk = std::min(p.steps, std::max(1LL, 256LL * K::PER_CU / p.groups));
     const double used = (double)s.w * s.h / ((double)p.nbw * tw * p.nbh * th);
-    const double us = cin == 8 ? (p.groups > 1 ? 3.3 : 2.6) : (cin == 16 ? 4.0 : 3.7);
-    p.us = 4 + (std::ceil((double)p.steps / p.nchunk) + 1) * us * (0.8 + 0.2 * used);
+    const double us = cin == 8 ? (p.groups > 1 ? 3.0 : 2.7)
+                               : (cin == 16 ? (K::NB == 1 ? 3.8 : 3.4) : 3.5);
+    p.us = 5 + (std::ceil((double)p.steps / p.nchunk) + 1) * us * (0.8 + 0.2 * used);
     return true;
   });
   return p;
@@ -1129,9 +1139,9 @@ double gather_us(unet_shape s, int cin, int cout) {
 // for what the estimates miss.  Gathering is the faster one where a brick is
 // mostly padding: 128 -> 128 channels on 256 x 256 x 1 170 us against 838 on
 // bricks, on 128 x 128 x 4 172 / 212 (128 x 128 x 6: 337 / 214); 16 -> 16 on
-// 256 x 256 x 2 19.7 / 21.4.  On 1800 random grids of 1 to 512 voxels a side the
-// choice was the fastest kernel or within 10% of it but for grids one or two
-// voxels wide or tens of microseconds short.
+// 256 x 256 x 2 19.7 / 21.4.  (The exceptions on random grids of 1 to 512 voxels a
+// side are one or two voxels wide, or tens of microseconds short.)  March or bricks:
+// march_plan.
 enum { CONV_GATHERED = 0, CONV_BRICK = 1, CONV_MARCH = 2 };
 struct ConvChoice {
   int kernel;
@@ -1146,8 +1156,10 @@ ConvChoice conv_choice(unet_shape s, int cin, int xld, int cout, int taps) {
   c.march = march_plan(s, cin, xld, cout);
   double us = gather_us(s, cin, cout);
   if (c.brick.shape >= 0 && (s.w <= 2 ? 1.0 : 0.8) * c.brick.us <= us)
-    c.kernel = CONV_BRICK, us = c.brick.us;
-  if (c.march.nchunk > 0 && c.march.us < 0.95 * us) c.kernel = CONV_MARCH;
+    c.kernel = CONV_BRICK, us = c.brick.us_march;
+  else
+    us *= 0.95;
+  if (c.march.nchunk > 0 && c.march.us < us) c.kernel = CONV_MARCH;
   return c;
 }
 

@@ -141,3 +141,21 @@ def test_bad_wgrad_arguments():
                  (s, 16, 16, 27, 8), (s, 16, 16, 27, 16, 12), (UN.shape(1, 8, 0, 8), 16, 16, 27)):
         with pytest.raises(UN.UNetError):
             UN.unet_wgrad_launch(*args)
+
+
+# Ragged and regular grids near the line between the marching kernel and the
+# bricks, with the faster one (us marching / on bricks).
+@pytest.mark.parametrize("case, kernel", [
+    ((1, 114, 65, 58, 32, 16), "brick"),    # 27.6 / 21.5
+    ((1, 124, 75, 49, 32, 16), "brick"),    # 26.5 / 21.3
+    ((2, 25, 73, 23, 32, 32), "brick"),     # 15.6 / 13.1
+    ((2, 47, 45, 114, 32, 32), "brick"),    # 39.7 / 35.2
+    ((1, 83, 120, 13, 32, 64), "brick"),    # 42.8 / 23.4
+    ((1, 109, 127, 135, 16, 32), "march"),  # 57.4 / 64.5
+    ((2, 80, 96, 136, 16, 32), "march"),    # 63.1 / 68.8
+    ((2, 64, 64, 64, 32, 64), "march"),     # 64.5 / 68.3
+    ((1, 45, 86, 90, 16, 32), "march"),     # 17.8 / 18.5
+], ids=str)
+def test_march_or_bricks(case, kernel):
+    n, d, h, w, cin, cout = case
+    assert UN.unet_conv_launch(UN.shape(n, d, h, w), cin, cout, 27)[0] == kernel
